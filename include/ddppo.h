@@ -17,7 +17,8 @@
  *     by the tile autotuner (ppo_autotune mode 1) allocates and frees a
  *     scratch output, and ppo_gemm_timer_arm creates HIP events.  With
  *     PPO_COLLECT_GRAPH, ppo_collect creates and keeps HIP graphs (the HIP
- *     runtime's memory) and one private capture stream per net.
+ *     runtime's memory), captured on a private stream that lives only as long
+ *     as the capture.
  *   - All work is enqueued on `stream` (a hipStream_t passed as void*;
  *     NULL = the null stream) and is asynchronous.  Shape, pointer and
  *     workspace errors are detected on the host before any launch and
@@ -214,7 +215,7 @@ ppo_status ppo_act(ppo_net* net, const ppo_act_io* io, void* ws, size_t ws_bytes
  * flags and, with PPO_COLLECT_TRIM, the contents of `lengths`).  The first
  * call with a new argument set runs the steps eagerly on `stream` (so the
  * tile table is tuned when tuning is on; the results are that call's
- * outputs) and then records them, on a private stream of the net's device,
+ * outputs) and then records them, on a private stream of that capture alone,
  * into a graph that later calls launch on `stream`.  A graph reads the
  * buffers' contents when it runs, not when it was captured, so the host may
  * refill obs, u, active, ... between launches; the buffers themselves must

@@ -84,8 +84,7 @@ struct ppo_net {
   // ppo_collect's captured act loops, keyed on the call's arguments, oldest first
   std::unordered_map<std::string, hipGraphExec_t> graphs;
   std::deque<std::string> graph_order;
-  hipStream_t cap_stream = nullptr;  // private capture stream (default priority)
-  int cap_device = -1;
+  int cap_device = -1;        // the device those graphs live on
 };
 
 // Makes the net's tile table visible to the GEMM launchers for one call.
@@ -776,7 +775,6 @@ static int collect_drop(ppo_net* net, size_t keep) {
 void ppo_net_destroy(ppo_net* net) {
   if (!net) return;
   collect_drop(net, 0);
-  if (net->cap_stream) (void)hipStreamDestroy(net->cap_stream);
   for (hipEvent_t e : net->timer_ev)
     if (e) (void)hipEventDestroy(e);
   delete net;
@@ -1011,7 +1009,7 @@ ppo_status ppo_collect(ppo_net* net, const ppo_collect_io* io, int flags, void* 
   if (trim) put(rows.data(), rows.size() * sizeof(int));
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return check_launch();
-  if (net->cap_stream && net->cap_device != dev)
+  if (net->cap_device >= 0 && net->cap_device != dev)
     return fail(PPO_EINVAL, "the net's act graphs live on device %d, not %d", net->cap_device, dev);
   auto hit = net->graphs.find(key);
   if (hit != net->graphs.end()) {
@@ -1020,24 +1018,28 @@ ppo_status ppo_collect(ppo_net* net, const ppo_collect_io* io, int flags, void* 
   }
   // first call: eager steps (their results stand), then capture on the private stream
   if (const ppo_status st = collect_run(net, io, rows, trim, ws, ws_bytes, s); st != PPO_OK) return st;
-  if (!net->cap_stream) {
-    if (hipStreamCreateWithFlags(&net->cap_stream, hipStreamNonBlocking) != hipSuccess) return check_launch();
-    net->cap_device = dev;
-  }
+  // the capture's private stream (default priority) lives only as long as the capture: a stream
+  // kept per net holds one of the process's few hardware queues, and once three nets had taken
+  // theirs the learner's cooperative launches dragged every launch around them (one minibatch of
+  // 256 frames at 256x256 bfloat16: 27.4 ms instead of 15.5 ms)
+  hipStream_t cap = nullptr;
+  if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) return check_launch();
+  net->cap_device = dev;
   collect_drop(net, kMaxCollectGraphs - 1);
   // the launch timer stays out of captured graphs (its events are re-armed and destroyed by the host)
   const int tu = net->timer_unit;
   net->timer_unit = -1;
   hipGraph_t g = nullptr;
   ppo_status st = PPO_OK;
-  if (hipStreamBeginCapture(net->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+  if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
     st = check_launch();
   } else {
-    st = collect_run(net, io, rows, trim, ws, ws_bytes, net->cap_stream);
-    const hipError_t e = hipStreamEndCapture(net->cap_stream, &g);
+    st = collect_run(net, io, rows, trim, ws, ws_bytes, cap);
+    const hipError_t e = hipStreamEndCapture(cap, &g);
     if (st == PPO_OK && (e != hipSuccess || !g)) st = fail(PPO_EDEVICE, "act graph capture failed: %s", hipGetErrorString(e));
   }
   net->timer_unit = tu;
+  (void)hipStreamDestroy(cap);
   hipGraphExec_t exec = nullptr;
   if (st == PPO_OK && hipGraphInstantiate(&exec, g, nullptr, nullptr, 0) != hipSuccess)
     st = fail(PPO_EDEVICE, "act graph instantiation failed: %s", hipGetErrorString(hipGetLastError()));
