@@ -634,11 +634,15 @@ void encoder_bwd(const Ctx& c, const float* dfeat) {
         TimerScope ts(n, b.c1, 2);
         gemm_conv_wgrad(n->prec, g1, xin, GU, epi(c.grad + u1.w, (int)K1), kSplitKBytes, c.splitk(), c.s);
       }
-      // projection shortcut: writes dX, then c1's data gradient accumulates
-      unit_bwd(c, b.ds, GR, nullptr, false, xin, GD, GB, false, nullptr);
-      TimerScope ts(n, b.c1, 1);
-      gemm_conv_dgrad(n->prec, g1, GU, c.wt(u1.w), c.at<void>(w.wT), epi(GB, u1.Cin, nullptr, 0, 1),
-                      kSplitKBytes, c.splitk(), c.s);
+      // c1's data gradient writes dX, then the projection shortcut's accumulates:
+      // a strided shortcut reaches a quarter of the pixels and touches only
+      // those (the other way round the rest are zeroed and read back first)
+      {
+        TimerScope ts(n, b.c1, 1);
+        gemm_conv_dgrad(n->prec, g1, GU, c.wt(u1.w), c.at<void>(w.wT), epi(GB, u1.Cin), kSplitKBytes, c.splitk(),
+                        c.s);
+      }
+      unit_bwd(c, b.ds, GR, nullptr, false, xin, GD, GB, true, nullptr);
     } else {
       unit_bwd(c, b.c1, GD, c.at(w.a[b.c1]), false, xin, GU, GB, true, nullptr);
     }

@@ -1,0 +1,75 @@
+"""The kernels that read four elements at a time, at the sizes where that can
+go wrong: frames at every element alignment, gradients with a remainder past
+the last quad, pooling at odd channel-quad counts, and the packing of
+minibatches whose lengths reach every form (one env, length 1, more frames
+than a workgroup)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from synth import rollout as R
+from tests.gpu_util import DEV, random_record, to_device
+from tests.nets import MINI_RESNET, TINY_PLUS
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width", [4, 12])
+def test_encode_is_the_same_at_any_frame_alignment(P, dtype, width):
+    """Frames aligned to a pixel pair take the wide pooling kernel, others the
+    elementwise one: both form 0.25 ((a + b) + (c + d)), bit for bit."""
+    net = dataclasses.replace(MINI_RESNET, base_width=width, gn_groups=2)
+    n = P.Net(net, dtype)
+    params = torch.tensor(R.init_params(net, 1, random_affine=True), device=DEV)
+    lp = P.cast_bf16(params) if dtype == "bf16" else None
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    F, k = 3, 3 * net.in_ch * net.in_hw ** 2
+    x = torch.rand(k, generator=torch.Generator().manual_seed(2)).to(td).to(DEV)
+    ref = None
+    for off in range(4):
+        print(f"encode {dtype} width {width}: frames {off} elements past an aligned address", flush=True)
+        buf = torch.zeros(k + 4, dtype=td, device=DEV)
+        buf[off:off + k] = x
+        out = n.encode(buf[off:off + k].view(F, net.in_ch, net.in_hw, net.in_hw), params, lp)
+        torch.cuda.synchronize()
+        ref = out if ref is None else ref
+        assert torch.isfinite(out).all() and torch.equal(out, ref), off
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 1027, 4 * 256 * 1024 + 3])
+def test_adam_finds_a_non_finite_gradient_anywhere(P, n):
+    print(f"adam check of {n} gradients", flush=True)
+    for bad in (float("inf"), float("-inf"), float("nan")):
+        for i in sorted({0, n // 2, max(n - 4, 0), max(n - 3, 0), max(n - 2, 0), n - 1}):
+            master = torch.ones(n, device=DEV)
+            opt = P.Adam(n, DEV, lr=1e-3, loss_scale=1.0, growth_interval=0)
+            g = torch.ones(n, device=DEV)
+            opt.step(master, g)
+            assert opt.state()["skipped"] == 0 and opt.state()["step"] == 1
+            before = master.clone()
+            g[i] = bad
+            opt.step(master, g)
+            assert opt.state()["skipped"] == 1 and torch.equal(master, before), (bad, i)
+
+
+@pytest.mark.parametrize("T,lens", [(1, [1]), (1, [1, 1, 1]), (130, [130]), (7, [7, 1, 1, 3]),
+                                    (300, [1, 300, 299, 2]), (3, [1 + i % 3 for i in range(256)])],
+                         ids=["one", "ones", "one_env", "short", "long", "256_envs"])
+def test_frame_packing(P, T, lens):
+    """dvalues of the loss head at V = 0 is -value_coef w ret of the frame's
+    (step, env): returns that number the cells show the packing (time-major,
+    longest env first).  A product of three float32 factors: 4 roundings."""
+    print(f"frame packing T={T} envs={len(lens)}", flush=True)
+    n, N = P.Net(TINY_PLUS, "f32"), len(lens)
+    rec = random_record(TINY_PLUS, T, N, 3, lengths=lens)
+    ro = to_device(rec)
+    ro["ret"] = torch.arange(1, T * N + 1, dtype=torch.float32, device=DEV).view(T, N)
+    F = sum(lens)
+    cfg = P.LossCfg()
+    dv = n.loss_head(ro, list(range(N)), lens, torch.zeros(F, n.A, device=DEV), torch.zeros(F, device=DEV), cfg)[1]
+    order = sorted(range(N), key=lambda e: -lens[e])
+    want = [-cfg.value_coef / (N * lens[e]) * (t * N + e + 1) for t in range(T) for e in order if lens[e] > t]
+    np.testing.assert_allclose(dv.cpu().numpy(), np.array(want), rtol=4 * 2.0 ** -23)
