@@ -781,7 +781,6 @@ def summarize_counters(csv_path):
             continue
         name = disp[i]["name"]
         k = "conv forward GEMM" if "ConvFwdProb" in name else \
-            "stem weight-gradient GEMM (channel-vector loads)" if "ConvWgradRTProb" in name else \
             "conv weight-gradient GEMM" if "ConvWgrad" in name \
             else "conv data-gradient GEMM" if "ConvDgrad" in name else "dense GEMM" if "DenseProb" in name \
             else _short(name)

@@ -11,8 +11,8 @@
 // vector loads, for operands contiguous along rows (transposed reads) the
 // lanes of a wavefront walk the rows so each of the 8 scalar loads is
 // coalesced; either way the chunk lands in LDS with one 16-byte write.
-// Operands read as 8-row vectors at one k (RT: the stem's weight gradient)
-// are staged two k at a time and stored as 8 row pairs (put8t2).
+// The weight gradient reads 4 rows x 4 k as four row vectors and transposes
+// them in registers (QUADS).
 //
 // bfloat16: v_mfma_f32_32x32x16_bf16 on 32x32 fragments.  float32: four
 // v_mfma_f32_16x16x4_f32 per 16-k step on 16x16 fragments.  A and B use the
@@ -290,59 +290,68 @@ struct ConvWgradProb {
   }
 };
 
-// Weight gradient with channel-vector chunks: a chunk is the 8 consecutive
-// rows m..m+7 (output channels co for A, (kh,kw,ci) for B) at one reduction
-// index r = (b,ho,wo), read as two float4 along the NHWC channel axis and
-// written transposed into the k-contiguous LDS rows.  Needs Co % 8 == 0 and
-// C % 4 == 0 (a B chunk spans one tap when C % 8 == 0, else two taps of 4).
-struct ConvWgradRTProb {
-  static constexpr int kKind = 4;
+// Weight gradient with channel quads: a unit is 4 consecutive channels (co for
+// A, ci of one tap for B) at 4 consecutive reduction indices r = (b,ho,wo),
+// four float4 loads along the NHWC channel axis, coalesced over the lanes.
+// Bound by vector instructions, not by memory latency (two K tiles in flight
+// gained nothing): a quarter of the loads and index arithmetic of the scalar
+// gather, the same conversions.  All weight gradients of 256 frames (54
+// launches): bfloat16 3.01 -> 1.95 ms, float32 4.25 -> 3.21 ms (its stem alone, 4
+// channels a tap, is slower than 8-row vectors stored transposed: 317 -> 360 us).
+// Needs Co % 4 == 0, C % 4 == 0 and 16-byte aligned x and dy.
+struct ConvWgradQProb {
+  static constexpr int kKind = 3;
   ConvGeo g;
-  FastDiv dHoWo, dWo;
+  FastDiv dC, dKW, dHoWo, dWo;
   const float* x;
   const float* dy;
   int M, N, K;  // M = Co, N = KH*KW*C, K = B*Ho*Wo
-  struct RA {
-    int co, ok;
+  int flat;     // 1x1, stride 1, no padding: reduction row r is row r of x
+  struct RU {
+    int c, kh, kw, ok;
   };
-  struct RB {
-    int kh0, kw0, ci0, kh1, kw1, ci1, nv;  // taps of rows n..n+3 and n+4..n+7; valid rows
-  };
-  DEV RA rowA(int m) const { return RA{m, m < M}; }
-  DEV RB rowB(int n) const {
-    RB r{0, 0, 0, 0, 0, 0, max(0, min(8, N - n))};
-    const int t0 = n / g.C, t1 = (n + 4) / g.C;
-    r.ci0 = n - t0 * g.C;
-    r.kh0 = t0 / g.KW;
-    r.kw0 = t0 - r.kh0 * g.KW;
-    r.ci1 = n + 4 - t1 * g.C;
-    r.kh1 = t1 / g.KW;
-    r.kw1 = t1 - r.kh1 * g.KW;
+  // tile-table kind: that of the kernel which took these sizes when the table's format was laid down
+  int kind() const { return g.C % 8 == 0 || g.Co % 8 != 0 ? 3 : 4; }
+  DEV RU rowA(int m) const { return RU{m, 0, 0, m < M}; }
+  DEV RU rowB(int n) const {
+    RU r{0, 0, 0, n < N};
+    if (r.ok) {
+      const int tap = dC.div(n);
+      r.c = n - tap * g.C;
+      r.kh = dKW.div(tap);
+      r.kw = tap - r.kh * g.KW;
+    }
     return r;
   }
-  DEV void a8(const RA& r, int k, float v[8]) const {
-    if (!r.ok || k >= K) return zero8(v);
-    load8(dy + (size_t)k * g.Co + r.co, v);
+  DEV void rows4(const float* base, int ld, int k, int kend, float4 v[4]) const {
+    const float* q = base + (size_t)k * ld;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      v[e] = k + e < kend ? *(const float4*)(q + (size_t)e * ld) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  DEV void b8(const RB& r, int k, float v[8]) const {
-    if (r.nv <= 0 || k >= K) return zero8(v);
-    const int b = dHoWo.div(k), q = k - b * g.Ho * g.Wo;
-    const int ho = dWo.div(q), wo = q - ho * g.Wo;
-    const int hb = ho * g.stride - g.pad, wb = wo * g.stride - g.pad;
-    const float* xb = x + (size_t)b * g.H * g.W * g.C;
-    auto quad = [&](int kh, int kw, int ci, float* o) {
-      const int hi = hb + kh, wi = wb + kw;
-      if ((unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W) {
-        const float4 t = *(const float4*)(xb + ((size_t)hi * g.W + wi) * g.C + ci);
-        o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
-      } else {
-        o[0] = o[1] = o[2] = o[3] = 0.f;
+  DEV void a44(const RU& r, int k, int kend, float4 v[4]) const {
+    rows4(dy + (r.ok ? r.c : 0), g.Co, k, r.ok ? kend : 0, v);
+  }
+  DEV void b44(const RU& r, int k, int kend, float4 v[4]) const {
+    if (!r.ok) kend = 0;
+    if (flat) return rows4(x + r.c, g.C, k, kend, v);
+    int b = dHoWo.div(k);
+    const int q = k - b * g.Ho * g.Wo;
+    int ho = dWo.div(q), wo = q - ho * g.Wo;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int hi = ho * g.stride - g.pad + r.kh, wi = wo * g.stride - g.pad + r.kw;
+      const bool in = k + e < kend && (unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W;
+      v[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (in) v[e] = *(const float4*)(x + (((size_t)b * g.H + hi) * g.W + wi) * g.C + r.c);
+      if (++wo == g.Wo) {
+        wo = 0;
+        if (++ho == g.Ho) {
+          ho = 0;
+          ++b;
+        }
       }
-    };
-    quad(r.kh0, r.kw0, r.ci0, v);
-    if (r.nv > 4) quad(r.kh1, r.kw1, r.ci1, v + 4);
-    else v[4] = v[5] = v[6] = v[7] = 0.f;
-    for (int e = r.nv; e < 4; ++e) v[e] = 0.f;
+    }
   }
 };
 
@@ -388,25 +397,28 @@ struct DenseProb {
 template <class P> struct WeightBytes { static constexpr int v = 0; };
 template <typename TW> struct WeightBytes<ConvFwdProb<TW>> { static constexpr int v = (int)sizeof(TW); };
 
-// Is the operand contiguous along rows (so lanes should walk rows)?  RT:
-// chunks are 8 rows at one k (vector loads along rows, transposed LDS writes).
+// Is the operand contiguous along rows (so lanes should walk rows)?  QUADS:
+// units are 4 rows x 4 k (vector loads along rows, transposed in registers).
 template <class P> struct Layout;
-template <> struct Layout<ConvWgradRTProb> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, A_RT = true, B_RT = true;
+template <> struct Layout<ConvWgradQProb> {
+  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = true;
 };
 template <typename TW> struct Layout<ConvFwdProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, A_RT = false, B_RT = false;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false;
 };
 template <typename TW> struct Layout<ConvDgradProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, A_RT = false, B_RT = false;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false;
 };
 template <> struct Layout<ConvWgradProb> {
-  static constexpr bool A_ROWS = true, B_ROWS = true, A_RT = false, B_RT = false;
+  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = false;
 };
 template <typename A_, typename B_, bool TA, bool TB>
 struct Layout<DenseProb<A_, B_, TA, TB>> {
-  static constexpr bool A_ROWS = TA, B_ROWS = TB, A_RT = false, B_RT = false;
+  static constexpr bool A_ROWS = TA, B_ROWS = TB, QUADS = false;
 };
+// Tile-table kind of a problem.
+template <class P> int kind_of(const P&) { return P::kKind; }
+inline int kind_of(const ConvWgradQProb& p) { return p.kind(); }
 
 // ------------------------------------------------------------- MFMA
 template <typename TC>
@@ -478,23 +490,24 @@ DEV void put8(bf16_t* d, const float v[8], bf16_t* lo) {
   }
 }
 
-// Two chunks at k and k+1 -> columns k, k+1 of 8 consecutive LDS rows
-// (stride ld elements; k even): one 64-bit (float pair) or 32-bit (bfloat16
-// pair) store per row.  The lanes of a wavefront walk k, so each store
-// instruction covers consecutive LDS words of a row: a column of 16-bit
-// stores down the rows would put most lanes of a wavefront on a few banks.
-DEV void put8t2(float* d, int ld, const float v0[8], const float v1[8], float*) {
-#pragma unroll
-  for (int e = 0; e < 8; ++e) *(float2*)(d + e * ld) = make_float2(v0[e], v1[e]);
+// 4 rows x 4 k (v[e] = the rows' values at k+e) -> 4 consecutive LDS rows
+// (stride ld elements): one 16-byte (float) or 8-byte (bfloat16) store a row.
+DEV void put44(float* d, int ld, const float4 v[4], float*) {
+  *(float4*)d = make_float4(v[0].x, v[1].x, v[2].x, v[3].x);
+  *(float4*)(d + ld) = make_float4(v[0].y, v[1].y, v[2].y, v[3].y);
+  *(float4*)(d + 2 * ld) = make_float4(v[0].z, v[1].z, v[2].z, v[3].z);
+  *(float4*)(d + 3 * ld) = make_float4(v[0].w, v[1].w, v[2].w, v[3].w);
 }
-DEV void put8t2(bf16_t* d, int ld, const float v0[8], const float v1[8], bf16_t* lo) {
+DEV void put44(bf16_t* d, int ld, const float4 v[4], bf16_t* lo) {
+  const float* f = (const float*)v;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const uint32_t h = pk_bf16(v0[e], v1[e]);
-    *(uint32_t*)(d + e * ld) = h;
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t h0 = pk_bf16(f[j], f[4 + j]), h1 = pk_bf16(f[8 + j], f[12 + j]);
+    *(uint2*)(d + j * ld) = make_uint2(h0, h1);
     if (lo) {
-      const float a = __uint_as_float(h << 16), b = __uint_as_float(h & 0xffff0000u);
-      *(uint32_t*)(lo + e * ld) = pk_bf16(v0[e] - a, v1[e] - b);
+      const uint32_t l0 = pk_bf16(f[j] - __uint_as_float(h0 << 16), f[4 + j] - __uint_as_float(h0 & 0xffff0000u));
+      const uint32_t l1 = pk_bf16(f[8 + j] - __uint_as_float(h1 << 16), f[12 + j] - __uint_as_float(h1 & 0xffff0000u));
+      *(uint2*)(lo + j * ld) = make_uint2(l0, l1);
     }
   }
 }
@@ -509,13 +522,13 @@ __global__ void __launch_bounds__(256) gemm_kernel(Prob p, Epi e, int tiles_n, i
   constexpr int FM = WTM / FR, FN = WTN / FR;
   static_assert(WGM * WGN == 4 && FM >= 1 && FN >= 1, "bad tile");
   constexpr int LDK = BK + 16 / (int)sizeof(TC);  // padded LDS row (elements)
-  constexpr bool AR = Layout<Prob>::A_ROWS, BR = Layout<Prob>::B_ROWS;
-  constexpr bool ART = Layout<Prob>::A_RT, BRT = Layout<Prob>::B_RT;
-  // work units per K tile: a chunk (one row, 8 k), or for RT operands two
-  // chunks (8 rows at k and k+1, stored by put8t2)
-  constexpr int CA = ART ? (BM / 8) * (BK / 2) : BM * BK / 8, CB = BRT ? (BN / 8) * (BK / 2) : BN * BK / 8;
+  constexpr bool AR = Layout<Prob>::A_ROWS, BR = Layout<Prob>::B_ROWS, QUADS = Layout<Prob>::QUADS;
+  // chunks (one row, 8 k) per K tile and thread
+  constexpr int CA = BM * BK / 8, CB = BN * BK / 8;
   constexpr int QA = (CA + 255) / 256, QB = (CB + 255) / 256;
-  constexpr int VA = ART ? 2 : 1, VB = BRT ? 2 : 1;
+  // QUADS: units (4 rows, 4 k) of A, then of B; a wavefront's units are all of one operand
+  constexpr int UA = BM * BK / 16, UB = BN * BK / 16, QU = (UA + UB + 255) / 256;
+  static_assert(UA % 64 == 0 && UB % 64 == 0, "units of a wavefront");
   constexpr int NSPL = SPLIT ? 2 : 1;
   __shared__ __attribute__((aligned(16))) TC sA[NSPL][2][BM * LDK];
   __shared__ __attribute__((aligned(16))) TC sB[2][BN * LDK];
@@ -527,27 +540,12 @@ __global__ void __launch_bounds__(256) gemm_kernel(Prob p, Epi e, int tiles_n, i
   const int kend = min(p.K, kbeg + k_per_split);
   const int wm0 = (wave / WGN) * WTM, wn0 = (wave % WGN) * WTN;
 
-  // unit c -> (row, k offset): lanes walk k for k-contiguous operands and
+  // chunk c -> (row, k offset): lanes walk k for k-contiguous operands and
   // rows for row-contiguous ones
-  // (RT: unit c -> first row 8*(c / (BK/2)) of an 8-row group and the k
-  // pair 2*(c % (BK/2)): lanes walk the k pairs)
-  auto a_row = [&](int c) { return ART ? (c / (BK / 2)) * 8 : AR ? c % BM : c / (BK / 8); };
-  auto a_kc = [&](int c) { return ART ? (c % (BK / 2)) * 2 : AR ? (c / BM) * 8 : (c % (BK / 8)) * 8; };
-  auto b_row = [&](int c) { return BRT ? (c / (BK / 2)) * 8 : BR ? c % BN : c / (BK / 8); };
-  auto b_kc = [&](int c) { return BRT ? (c % (BK / 2)) * 2 : BR ? (c / BN) * 8 : (c % (BK / 8)) * 8; };
-
-  typename Prob::RA ra[QA];
-  typename Prob::RB rb[QB];
-#pragma unroll
-  for (int q = 0; q < QA; ++q) {
-    const int c = tid + 256 * q;
-    ra[q] = p.rowA(c < CA ? m0 + a_row(c) : 1 << 30);
-  }
-#pragma unroll
-  for (int q = 0; q < QB; ++q) {
-    const int c = tid + 256 * q;
-    rb[q] = p.rowB(c < CB ? n0 + b_row(c) : 1 << 30);
-  }
+  auto a_row = [&](int c) { return AR ? c % BM : c / (BK / 8); };
+  auto a_kc = [&](int c) { return AR ? (c / BM) * 8 : (c % (BK / 8)) * 8; };
+  auto b_row = [&](int c) { return BR ? c % BN : c / (BK / 8); };
+  auto b_kc = [&](int c) { return BR ? (c / BN) * 8 : (c % (BK / 8)) * 8; };
 
   typename MM::Acc acc[FM][FN];
 #pragma unroll
@@ -555,55 +553,11 @@ __global__ void __launch_bounds__(256) gemm_kernel(Prob p, Epi e, int tiles_n, i
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = MM::zero();
 
-  float va[QA][VA][8], vb[QB][VB][8];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < QA; ++q) {
-      const int c = tid + 256 * q;
-      const int k = k0 + a_kc(c);
-#pragma unroll
-      for (int h = 0; h < VA; ++h) {
-        if (c < CA && k + h < kend) p.a8(ra[q], k + h, va[q][h]);
-        else zero8(va[q][h]);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const int c = tid + 256 * q;
-      const int k = k0 + b_kc(c);
-#pragma unroll
-      for (int h = 0; h < VB; ++h) {
-        if (c < CB && k + h < kend) p.b8(rb[q], k + h, vb[q][h]);
-        else zero8(vb[q][h]);
-      }
-    }
-  };
-  auto sstore = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < QA; ++q) {
-      const int c = tid + 256 * q;
-      if (c < CA) {
-        const int o = a_row(c) * LDK + a_kc(c);
-        if constexpr (ART)
-          put8t2(&sA[0][buf][o], LDK, va[q][0], va[q][VA - 1], SPLIT ? &sA[NSPL - 1][buf][o] : (TC*)nullptr);
-        else
-          put8(&sA[0][buf][o], va[q][0], SPLIT ? &sA[NSPL - 1][buf][o] : (TC*)nullptr);
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const int c = tid + 256 * q;
-      if (c < CB) {
-        if constexpr (BRT)
-          put8t2(&sB[buf][b_row(c) * LDK + b_kc(c)], LDK, vb[q][0], vb[q][VB - 1], (TC*)nullptr);
-        else
-          put8(&sB[buf][b_row(c) * LDK + b_kc(c)], vb[q][0], (TC*)nullptr);
-      }
-    }
-  };
-
-  const int ntiles = kbeg < kend ? (kend - kbeg + BK - 1) / BK : 0;
-  if (ntiles > 0) {
+  // the main loop over K tiles: gload(k0) fetches a tile into registers,
+  // sstore(buf) converts and writes it to LDS
+  auto mainloop = [&](auto& gload, auto& sstore) {
+    const int ntiles = kbeg < kend ? (kend - kbeg + BK - 1) / BK : 0;
+    if (ntiles <= 0) return;
     gload(kbeg);
     sstore(0);
     __syncthreads();
@@ -627,6 +581,84 @@ __global__ void __launch_bounds__(256) gemm_kernel(Prob p, Epi e, int tiles_n, i
       if (t + 1 < ntiles) sstore(cur ^ 1);
       __syncthreads();
     }
+  };
+  if constexpr (QUADS) {
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    typename Prob::RU ru[QU];
+    int uo[QU], uk[QU];  // LDS offset, k offset
+    float4 vu[QU][4];
+    auto is_a = [&](int q) { return wv + 4 * q < UA / 64; };
+    auto live = [&](int q) { return wv + 4 * q < (UA + UB) / 64; };
+#pragma unroll
+    for (int q = 0; q < QU; ++q) {
+      // lanes: 4 row quads (64 bytes of a memory row) by the 8 k groups, so
+      // that the stores of 16 (float) or 32 (bfloat16) lanes, whose rows lie
+      // 4 LDK apart, cover every LDS bank once
+      const int u = tid + 256 * q - (is_a(q) ? 0 : UA);
+      const int row = ((u & 3) + (u >> 5) * 4) * 4;
+      uk[q] = ((u >> 2) & 7) * 4;
+      uo[q] = row * LDK + uk[q];
+      ru[q] = is_a(q) ? p.rowA(m0 + row) : p.rowB(live(q) ? n0 + row : 1 << 30);
+    }
+    auto gload = [&](int k0) {
+#pragma unroll
+      for (int q = 0; q < QU; ++q) {
+        if (is_a(q)) p.a44(ru[q], k0 + uk[q], kend, vu[q]);
+        else if (live(q)) p.b44(ru[q], k0 + uk[q], kend, vu[q]);
+      }
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+      for (int q = 0; q < QU; ++q) {
+        if (is_a(q)) put44(&sA[0][buf][uo[q]], LDK, vu[q], SPLIT ? &sA[NSPL - 1][buf][uo[q]] : (TC*)nullptr);
+        else if (live(q)) put44(&sB[buf][uo[q]], LDK, vu[q], (TC*)nullptr);
+      }
+    };
+    mainloop(gload, sstore);
+  } else {
+    typename Prob::RA ra[QA];
+    typename Prob::RB rb[QB];
+#pragma unroll
+    for (int q = 0; q < QA; ++q) {
+      const int c = tid + 256 * q;
+      ra[q] = p.rowA(c < CA ? m0 + a_row(c) : 1 << 30);
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int c = tid + 256 * q;
+      rb[q] = p.rowB(c < CB ? n0 + b_row(c) : 1 << 30);
+    }
+    float va[QA][8], vb[QB][8];
+    auto gload = [&](int k0) {
+#pragma unroll
+      for (int q = 0; q < QA; ++q) {
+        const int c = tid + 256 * q;
+        const int k = k0 + a_kc(c);
+        if (c < CA && k < kend) p.a8(ra[q], k, va[q]);
+        else zero8(va[q]);
+      }
+#pragma unroll
+      for (int q = 0; q < QB; ++q) {
+        const int c = tid + 256 * q;
+        const int k = k0 + b_kc(c);
+        if (c < CB && k < kend) p.b8(rb[q], k, vb[q]);
+        else zero8(vb[q]);
+      }
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+      for (int q = 0; q < QA; ++q) {
+        const int c = tid + 256 * q;
+        const int o = a_row(c) * LDK + a_kc(c);
+        if (c < CA) put8(&sA[0][buf][o], va[q], SPLIT ? &sA[NSPL - 1][buf][o] : (TC*)nullptr);
+      }
+#pragma unroll
+      for (int q = 0; q < QB; ++q) {
+        const int c = tid + 256 * q;
+        if (c < CB) put8(&sB[buf][b_row(c) * LDK + b_kc(c)], vb[q], (TC*)nullptr);
+      }
+    };
+    mainloop(gload, sstore);
   }
 
   if (e.gm_p > 0 && (e.partial || !e.gm_split_only)) {

@@ -218,12 +218,19 @@ int run(const Prob& p, Epi e, size_t partial_bytes, float* partial, hipStream_t 
   const bool act = e.act && defer;
   const int min_split = act ? (int)std::max<long>(1, std::min<long>({4L, (long)p.K / 64, cap})) : 1;
   splits = std::max(splits, min_split);
+  // Channel quads: a 64x64 tile gives every thread one unit and more
+  // workgroups than the wider or narrower tiles, some of whose threads idle
+  // (256 frames, bfloat16: 128 x 32 products 74 -> 55 us, 32 x 128 ones 86 ->
+  // 49).  Not for float32 rows of which a 64-row tile pads half: those are
+  // bound by the matrix cores (32 x 288: 145 us against 113).  The K split stays
+  // that of the tile chosen above, so the sums do not change.
+  if (Layout<Prob>::QUADS && t != T128x128 && !(prec == 0 && p.M <= 32 && p.N > 128)) t = T64x64;
   GemmTune* tu = g_gemm_tune;
   if (tu) {
     // a deferred product (its partial tiles summed by the consumer) is tuned
     // on its own key, timed with the ordered reduction as the consumer's
     // stand-in; an act-step product on another
-    const std::array<long long, 5> key{Prob::kKind, p.M, p.N, p.K,
+    const std::array<long long, 5> key{kind_of(p), p.M, p.N, p.K,
                                        2 * prec + (int)SPLIT + 4 * (int)defer + 8 * (int)act};
     auto it = tu->best.find(key);
     if (it == tu->best.end() && tu->tuning && !capturing(s))
@@ -341,10 +348,11 @@ void gemm_conv_dgrad(int prec, const ConvGeo& g, const float* dy, const void* w,
 void gemm_conv_wgrad(int prec, const ConvGeo& g, const float* x, const float* dy, Epi e, size_t pb,
                      float* partial, hipStream_t s) {
   const int M = g.Co, N = g.KH * g.KW * g.C, K = g.B * g.Ho * g.Wo;
-  // channel-vector chunks pay for their transposed LDS writes only where the
-  // scalar gather is worst: fewer than 8 input channels per tap (the stem)
-  if (g.Co % 8 == 0 && g.C % 8 != 0 && g.C % 4 == 0 && (((uintptr_t)x | (uintptr_t)dy) & 15) == 0) {
-    ConvWgradRTProb p{g, fast_div(g.Ho * g.Wo), fast_div(g.Wo), x, dy, M, N, K};
+  // channel quads wherever every quad is one aligned vector of one tap; an
+  // input of other than 4n channels takes scalar loads
+  if (g.Co % 4 == 0 && g.C % 4 == 0 && (((uintptr_t)x | (uintptr_t)dy) & 15) == 0) {
+    ConvWgradQProb p{g, fast_div(g.C), fast_div(g.KW), fast_div(g.Ho * g.Wo), fast_div(g.Wo), x, dy, M, N, K,
+                     g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0};
     run_prec(p, e, prec, true, pb, partial, s);
     return;
   }

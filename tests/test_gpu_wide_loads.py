@@ -1,6 +1,6 @@
 """The kernels that read four elements at a time, at the sizes where that can
 go wrong: frames at every element alignment, gradients with a remainder past
-the last quad, pooling at odd channel-quad counts, and the packing of
+the last quad, weight gradients on every tile, pooling at odd channel-quad counts, and the packing of
 minibatches whose lengths reach every form (one env, length 1, more frames
 than a workgroup)."""
 import dataclasses
@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from synth import rollout as R
-from tests.gpu_util import DEV, random_record, to_device
+from tests.gpu_util import DEV, assert_close, random_record, to_device
 from tests.nets import MINI_RESNET, TINY_PLUS
 
 pytestmark = pytest.mark.gpu
@@ -73,3 +73,37 @@ def test_frame_packing(P, T, lens):
     order = sorted(range(N), key=lambda e: -lens[e])
     want = [-cfg.value_coef / (N * lens[e]) * (t * N + e + 1) for t in range(T) for e in order if lens[e] > t]
     np.testing.assert_allclose(dv.cpu().numpy(), np.array(want), rtol=4 * 2.0 ** -23)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width", [4, 12])
+def test_weight_gradient_tiles(P, dtype, width):
+    """The convolutions' weight gradients forced onto every tile shape, split
+    over K and not, at widths and frame counts with ragged tiles (7 frames, 1x1
+    to 16x16 maps: reductions of 7 to 1792 rows, 4 to 192 channels): the gradient
+    is that of the tuned tiles up to the order of float32 sums."""
+    print(f"weight gradient tiles {dtype} width {width}", flush=True)
+    net = dataclasses.replace(MINI_RESNET, base_width=width)
+    lengths, envs = [3, 2, 2], [0, 1, 2]
+    rec = random_record(net, 3, 3, 46, lengths=lengths, bf16=dtype == "bf16")
+    n = P.Net(net, dtype)
+    params = torch.tensor(R.init_params(net, 45, random_affine=True), device=DEV)
+    lp = P.cast_bf16(params) if dtype == "bf16" else None
+    ro, scale = to_device(rec, bf16=dtype == "bf16"), torch.tensor([1.0], device=DEV)
+
+    def grad():
+        g, _ = n.loss_backward(ro, envs, lengths, params, lp, P.LossCfg(), loss_scale=scale)
+        torch.cuda.synchronize()
+        return g.cpu().numpy().astype(np.float64)
+
+    n.autotune(1)
+    grad()
+    n.autotune(0)
+    g0 = grad()                                   # every product on its tuned tile
+    rows = [r for r in n.tile_table() if r[0] in (3, 4)]
+    assert {r[0] for r in rows} >= {3}
+    for tile in range(6):
+        for split in (None, 1):
+            print(f"  tile {tile} split {split}", flush=True)
+            n.tile_table([r[:5] + [tile, split or r[6]] for r in rows])
+            assert_close(f"gradient, tile {tile} split {split or 'tuned'}", grad(), g0, 1e-5)
