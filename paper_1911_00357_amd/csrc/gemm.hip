@@ -86,6 +86,31 @@ int splits_for(long tiles, long K) {
   return (int)std::max<long>(1, std::min<long>({want, kmax, 256}));
 }
 
+// The tile that is launched, given the one the K split was chosen for: the
+// split, and with it every sum, does not depend on it.  Times are of 256
+// frames, one product, in us.
+Tile launch_tile_of(Tile t, long M, long N, long K, int prec, bool quads) {
+  // Channel quads: a 64x64 tile gives every thread one unit and more workgroups
+  // than the wider or narrower tiles, some of whose threads idle (bfloat16:
+  // 128 x 32 products 74 -> 55, 32 x 128 ones 86 -> 49).  Not for float32 rows
+  // of which a 64-row tile pads half: those are bound by the matrix cores
+  // (32 x 288: 145 against 113).
+  if (quads) return t == T128x128 || (prec == 0 && M <= 32 && N > 128) ? t : T64x64;
+  // Others: with few K tiles a workgroup is mostly its first loads and its
+  // stores, and smaller tiles keep more of them in flight per CU (LDS 25 KB
+  // against 60).  bfloat16, M x N x K:
+  //   N <= 64 (65536 x 64 x 256: 128x64 29, 64x64 22; x 576: 37, 35)
+  if (prec == 1 && t == T128x64) return T64x64;
+  //   wide, K < 128 (262144 x 128 x 32 data gradient: 128x128 171, 64x64 98, 64x128 106)
+  //   wide, longer K (65536 x 256 x 128: 128x128 57, 64x64 41, 64x128 37)
+  if (t == T128x128) return K < 128 ? T64x64 : T64x128;
+  // float32, wide, short K (262144 x 128 x 32 data gradient: 128x64 173, 64x64
+  // 125); not from K = 256 (16384 x 512 x 256 data gradient: 73, 76) nor for N
+  // <= 64 (65536 x 64 x 576 data gradient: 67, 80)
+  if (prec == 0 && t == T128x64 && N > 64 && K < 256) return T64x64;
+  return t;
+}
+
 template <class Prob, typename TC, int BM, int BN, int WGM, int WGN, bool SPLIT>
 int launch(const Prob& p, Epi e, int splits, float* partial, hipStream_t s, bool defer) {
   const int tiles_m = cdiv(p.M, BM), tiles_n = cdiv(p.N, BN);
@@ -218,13 +243,7 @@ int run(const Prob& p, Epi e, size_t partial_bytes, float* partial, hipStream_t 
   const bool act = e.act && defer;
   const int min_split = act ? (int)std::max<long>(1, std::min<long>({4L, (long)p.K / 64, cap})) : 1;
   splits = std::max(splits, min_split);
-  // Channel quads: a 64x64 tile gives every thread one unit and more
-  // workgroups than the wider or narrower tiles, some of whose threads idle
-  // (256 frames, bfloat16: 128 x 32 products 74 -> 55 us, 32 x 128 ones 86 ->
-  // 49).  Not for float32 rows of which a 64-row tile pads half: those are
-  // bound by the matrix cores (32 x 288: 145 us against 113).  The K split stays
-  // that of the tile chosen above, so the sums do not change.
-  if (Layout<Prob>::QUADS && t != T128x128 && !(prec == 0 && p.M <= 32 && p.N > 128)) t = T64x64;
+  t = launch_tile_of(t, p.M, p.N, p.K, prec, Layout<Prob>::QUADS);
   GemmTune* tu = g_gemm_tune;
   if (tu) {
     // a deferred product (its partial tiles summed by the consumer) is tuned

@@ -107,3 +107,36 @@ def test_weight_gradient_tiles(P, dtype, width):
             print(f"  tile {tile} split {split}", flush=True)
             n.tile_table([r[:5] + [tile, split or r[6]] for r in rows])
             assert_close(f"gradient, tile {tile} split {split or 'tuned'}", grad(), g0, 1e-5)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("width", [4, 12])
+def test_tile_shape_does_not_change_a_bit(P, dtype, width):
+    """The launched tile is chosen apart from the K split, so every convolution
+    product (forward, data and weight gradient; ragged tiles as above) forced
+    onto any tile at one split leaves the whole gradient bit for bit."""
+    print(f"tiles bit for bit {dtype} width {width}", flush=True)
+    net = dataclasses.replace(MINI_RESNET, base_width=width)
+    lengths, envs = [3, 2, 2], [0, 1, 2]
+    rec = random_record(net, 3, 3, 46, lengths=lengths, bf16=dtype == "bf16")
+    n = P.Net(net, dtype)
+    params = torch.tensor(R.init_params(net, 45, random_affine=True), device=DEV)
+    lp = P.cast_bf16(params) if dtype == "bf16" else None
+    ro, scale = to_device(rec, bf16=dtype == "bf16"), torch.tensor([1.0], device=DEV)
+
+    def grad():
+        g, s = n.loss_backward(ro, envs, lengths, params, lp, P.LossCfg(), loss_scale=scale)
+        torch.cuda.synchronize()
+        return g.clone(), s.clone()
+
+    n.autotune(1)
+    grad()
+    n.autotune(0)
+    rows = [r for r in n.tile_table() if r[0] in (1, 2, 3, 4)]
+    assert {1, 2, 3} <= {r[0] for r in rows}
+    g0, s0 = grad()
+    assert torch.isfinite(g0).all() and g0.abs().sum() > 0
+    for tile in range(6):
+        n.tile_table([r[:5] + [tile, r[6]] for r in rows])
+        g1, s1 = grad()
+        assert torch.equal(g1, g0) and torch.equal(s1, s0), tile
