@@ -78,17 +78,16 @@ struct PixDiv {
 
 // ---------------------------------------------------------------- forward
 // Workgroup: `pix` consecutive output pixels of one group; thread t owns
-// output channel t % og of pixel rows t / og + k (256 / og).  CG > 0: the
-// group's input width as a compile-time constant, so the 9 taps' channel
-// loads (float4, unconditional: an out-of-range tap reads the image origin
-// and is zeroed) are all issued before the products.
-template <typename TW, int CG>
+// output channel t % og of pixel rows t / og + k (256 / og).  An
+// out-of-range tap reads the image origin and is zeroed.  General form: any
+// group width; see gconv_tile_kernel.
+template <typename TW>
 __global__ void __launch_bounds__(kThreads) gconv_fwd_kernel(const float* __restrict__ x, const TW* __restrict__ w,
                                                             float* __restrict__ y, ConvGeo g, int G, int pix,
                                                             PixDiv dv) {
   extern __shared__ float ws[];  // [9][cg][og]
   constexpr bool BF = sizeof(TW) == 2;
-  const int cg = CG > 0 ? CG : g.C / G, og = g.Co / G, grp = blockIdx.y;
+  const int cg = g.C / G, og = g.Co / G, grp = blockIdx.y;
   const int kw9 = 9 * cg;
   stage_filters(w + (size_t)grp * og * kw9, og * kw9, ws, [=](int e) {
     const int co = e / kw9, k = e - co * kw9;                 // w[grp*og + co][k] -> ws[k][co]
@@ -110,19 +109,11 @@ __global__ void __launch_bounds__(kThreads) gconv_fwd_kernel(const float* __rest
       const bool ok = (unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W;
       const float* xp = xb + (ok ? ((size_t)hi * g.W + wi) * g.C : 0);
       const float* wp = ws + tap * cg * og + co;
-      if (CG > 0) {
-        float v[CG > 0 ? CG : 4];
+      for (int c4 = 0; c4 < cg; c4 += 4) {
+        float v[4];
+        ld4(xp + c4, v);
 #pragma unroll
-        for (int c4 = 0; c4 < CG / 4; ++c4) ld4(xp + 4 * c4, v + 4 * c4);
-#pragma unroll
-        for (int ci = 0; ci < CG; ++ci) acc = fmaf(ok ? opnd<BF>(v[ci]) : 0.f, wp[ci * og], acc);
-      } else {
-        for (int c4 = 0; c4 < cg; c4 += 4) {
-          float v[4];
-          ld4(xp + c4, v);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc = fmaf(ok ? opnd<BF>(v[e]) : 0.f, wp[(c4 + e) * og], acc);
-        }
+        for (int e = 0; e < 4; ++e) acc = fmaf(ok ? opnd<BF>(v[e]) : 0.f, wp[(c4 + e) * og], acc);
       }
     }
     y[(size_t)p * g.Co + grp * og + co] = acc;
@@ -133,14 +124,14 @@ __global__ void __launch_bounds__(kThreads) gconv_fwd_kernel(const float* __rest
 // dx[b][hi][wi][grp*cg + ci] = sum over taps (kh, kw) whose output pixel
 // ho = (hi + pad - kh) / stride is whole and in range, and over the group's
 // output channels co, of dy[b][ho][wo][grp*og + co] * w[grp*og + co][kh][kw][ci].
-// Stride 1 or 2.  OG > 0: the group's output width at compile time.
-template <typename TW, int OG>
+// Stride 1 or 2.  General form.
+template <typename TW>
 __global__ void __launch_bounds__(kThreads) gconv_dgrad_kernel(const float* __restrict__ dy,
                                                               const TW* __restrict__ w, float* __restrict__ dx,
                                                               ConvGeo g, int G, int pix, PixDiv dv,
                                                               int accumulate) {
   extern __shared__ float ws[];  // [9][og][cg]
-  const int cg = g.C / G, og = OG > 0 ? OG : g.Co / G, grp = blockIdx.y;
+  const int cg = g.C / G, og = g.Co / G, grp = blockIdx.y;
   const int kw9 = 9 * cg;
   stage_filters(w + (size_t)grp * og * kw9, og * kw9, ws, [=](int e) {
     const int co = e / kw9, k = e - co * kw9, tap = k / cg, ci = k - tap * cg;
@@ -164,19 +155,11 @@ __global__ void __launch_bounds__(kThreads) gconv_dgrad_kernel(const float* __re
       const bool ok = th >= 0 && tw >= 0 && ((th | tw) & sh) == 0 && ho < g.Ho && wo < g.Wo;
       const float* dp = db + (ok ? ((size_t)ho * g.Wo + wo) * g.Co : 0);
       const float* wp = ws + tap * og * cg + ci;
-      if (OG > 0) {
-        float v[OG > 0 ? OG : 4];
+      for (int c4 = 0; c4 < og; c4 += 4) {
+        float v[4];
+        ld4(dp + c4, v);
 #pragma unroll
-        for (int c4 = 0; c4 < OG / 4; ++c4) ld4(dp + 4 * c4, v + 4 * c4);
-#pragma unroll
-        for (int co = 0; co < OG; ++co) acc = fmaf(ok ? v[co] : 0.f, wp[co * cg], acc);
-      } else {
-        for (int c4 = 0; c4 < og; c4 += 4) {
-          float v[4];
-          ld4(dp + c4, v);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc = fmaf(ok ? v[e] : 0.f, wp[(c4 + e) * cg], acc);
-        }
+        for (int e = 0; e < 4; ++e) acc = fmaf(ok ? v[e] : 0.f, wp[(c4 + e) * cg], acc);
       }
     }
     float* o = dx + (size_t)p * g.C + grp * cg + ci;
@@ -269,12 +252,212 @@ __global__ void __launch_bounds__(kThreads) gconv_wgrad_kernel(const float* __re
   }
 }
 
+// ------------------------------------------------- register-tiled kernels
+// The same sums for groups of CG input and CG output channels (CG 4, 8, 16 or
+// 32): every output is the same chain of FMAs as above, only dealt to the
+// threads otherwise.  The kernels above read LDS (and L1) once or twice an FMA,
+// which bounds them; these read a float4 for 4 to 8 FMAs.
+//
+// Forward and data gradient (BWD; source dy, filters transposed).  Workgroup:
+// `pix` pixels of gpw neighbouring groups (64 to 128 contiguous bytes a pixel);
+// a thread makes 4 channels of NP pixels (2, or 1 where that would leave the
+// chip idle).  Filters in LDS as ws[group][tap][source channel][channel], 16
+// floats of padding a group against conflicts between groups.  128 frames of
+// the paper's net, bfloat16, widths 4 / 8 / 16 / 32, in us: forward 95 / 85 /
+// 155 / 290 -> 53 / 37 / 22 / 34, data gradient 55 / 45 / 81 / 206 -> 28 / 22 /
+// 21 / 26, at stride 2 151 / 228 / 552 (8 / 16 / 32) -> 54 / 44 / 52.
+template <typename TW, int CG, bool BWD, int NP>
+__global__ void __launch_bounds__(kThreads) gconv_tile_kernel(const float* __restrict__ src,
+                                                             const TW* __restrict__ w, float* __restrict__ dst,
+                                                             ConvGeo g, int gpw, int pix, PixDiv dv,
+                                                             int accumulate) {
+  extern __shared__ float ws[];
+  constexpr bool RND = !BWD && sizeof(TW) == 2;
+  constexpr int QL = CG / 4, K9 = 9 * CG, NE = CG * K9, GS = NE + 16, UN = CG <= 8 ? 3 : 1;
+  const int grp0 = blockIdx.y * gpw;
+  stage_filters(w + (size_t)grp0 * NE, gpw * NE, ws, [=](int e) {
+    const int gi = e / NE, q = e - gi * NE, co = q / K9, k = q - co * K9, tap = k / CG, ci = k - tap * CG;
+    return gi * GS + (BWD ? (tap * CG + co) * CG + ci : k * CG + co);
+  });
+  __syncthreads();
+  const int nl = gpw * QL, rows = kThreads / nl, l = threadIdx.x % nl, r0 = threadIdx.x / nl;
+  const int gi = l / QL, c4 = l % QL * 4;
+  const float* wg = ws + gi * GS + c4;
+  const int Hd = BWD ? g.H : g.Ho, Wd = BWD ? g.W : g.Wo, Cd = BWD ? g.C : g.Co;
+  const int Hs = BWD ? g.Ho : g.H, Ws = BWD ? g.Wo : g.W, Cs = BWD ? g.Co : g.C;
+  const int sh = g.stride == 2 ? 1 : 0;
+  const int p0 = blockIdx.x * pix, pend = min(g.B * Hd * Wd, p0 + pix);
+  for (int p = p0 + r0; p < pend; p += NP * rows) {
+    int pp[NP], h0[NP], w0[NP];
+    const float* sb[NP];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      pp[u] = min(p + u * rows, pend - 1);  // past the end: the last pixel again, not stored
+      const int b = dv.plane.div(pp[u]), q = pp[u] - b * Hd * Wd, h = dv.row.div(q);
+      sb[u] = src + (size_t)b * Hs * Ws * Cs + (grp0 + gi) * CG;
+      h0[u] = BWD ? h + g.pad : h * g.stride - g.pad;
+      w0[u] = BWD ? q - h * Wd + g.pad : (q - h * Wd) * g.stride - g.pad;
+    }
+    float acc[NP][4];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.f;
+#pragma unroll UN
+    for (int tap = 0; tap < 9; ++tap) {
+      const int kh = tap / 3, kw = tap - 3 * kh;
+      float v[NP][CG];
+#pragma unroll
+      for (int u = 0; u < NP; ++u) {
+        int hs, wsx;
+        bool ok;
+        if (BWD) {
+          const int th = h0[u] - kh, tw = w0[u] - kw;
+          hs = th >> sh;
+          wsx = tw >> sh;
+          ok = th >= 0 && tw >= 0 && ((th | tw) & sh) == 0 && hs < Hs && wsx < Ws;
+        } else {
+          hs = h0[u] + kh;
+          wsx = w0[u] + kw;
+          ok = (unsigned)hs < (unsigned)Hs && (unsigned)wsx < (unsigned)Ws;
+        }
+        const float* q = sb[u] + (ok ? ((size_t)hs * Ws + wsx) * Cs : 0);  // outside: the origin, zeroed
+#pragma unroll
+        for (int c = 0; c < CG; c += 4) ld4(q + c, v[u] + c);
+#pragma unroll
+        for (int c = 0; c < CG; ++c) v[u][c] = ok ? opnd<RND>(v[u][c]) : 0.f;
+      }
+      const float* wp = wg + tap * CG * CG;
+#pragma unroll
+      for (int c = 0; c < CG; ++c) {
+        float f[4];
+        ld4(wp + c * CG, f);
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[u][j] = fmaf(v[u][c], f[j], acc[u][j]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      if (p + u * rows >= pend) break;
+      float4* o = (float4*)(dst + (size_t)pp[u] * Cd + (grp0 + gi) * CG + c4);
+      float4 r = make_float4(acc[u][0], acc[u][1], acc[u][2], acc[u][3]);
+      if (accumulate) {
+        const float4 t = *o;
+        r = make_float4(t.x + r.x, t.y + r.y, t.z + r.z, t.w + r.w);
+      }
+      *o = r;
+    }
+  }
+}
+
+// Weight gradient of GPW groups over one chunk of output pixels: a thread owns
+// CO x 4 elements (unit (group, co block, k quad)), PT pixels staged at a time;
+// the next PT are loaded into registers while these are summed.  GPW, CO and T
+// are sized to fill most of the threads with units and to keep the staged
+// pixels within 40 KB of LDS; the wider the group, the fewer the chunks, so
+// a width of 32 has 9 wavefronts a workgroup.  128 frames, bfloat16, widths 4 /
+// 8 / 16 / 32, in us: 208 / 128 / 82 / 202 -> 65 / 40 / 31 / 29.
+template <int CG> struct WgradTile;
+template <> struct WgradTile<4> { static constexpr int GPW = 4, CO = 2, T = 128, PT = 32; };
+template <> struct WgradTile<8> { static constexpr int GPW = 4, CO = 4, T = 192, PT = 32; };
+template <> struct WgradTile<16> { static constexpr int GPW = 1, CO = 4, T = 192, PT = 64; };
+template <> struct WgradTile<32> { static constexpr int GPW = 1, CO = 4, T = 576, PT = 32; };
+
+template <bool BF, int CG>
+__global__ void __launch_bounds__(WgradTile<CG>::T) gconv_wgrad_tile_kernel(const float* __restrict__ x,
+                                                                           const float* __restrict__ dy,
+                                                                           float* __restrict__ part, ConvGeo g,
+                                                                           int pix, PixDiv dv) {
+  using W = WgradTile<CG>;
+  constexpr int GPW = W::GPW, CO = W::CO, T = W::T, PT = W::PT, QL = CG / 4, K9 = 9 * CG, NE = CG * K9;
+  constexpr int XR = GPW * K9, DR = GPW * CG;                  // floats of a pixel's x and dy rows
+  constexpr int NX = PT * XR / 4, ND = PT * DR / 4;            // float4 of a round
+  constexpr int LX = NX / T, LD = (ND + T - 1) / T;
+  constexpr int UG = CG / CO * (K9 / 4), U = GPW * UG;         // units
+  static_assert(NX % T == 0 && U <= T, "round");
+  __shared__ __attribute__((aligned(16))) float xs[PT * XR];   // [pixel][group][tap][ci]
+  __shared__ __attribute__((aligned(16))) float ds[PT * DR];   // [pixel][group][co]
+  const int tid = threadIdx.x, grp0 = blockIdx.y * GPW, plane = g.Ho * g.Wo;
+  const int p0 = blockIdx.x * pix, pend = min(g.B * plane, p0 + pix);
+  float4 vx[LX], vd[LD];
+  auto gload = [&](int pt) {
+#pragma unroll
+    for (int n = 0; n < LX; ++n) {
+      const int e = tid + n * T, i = e / (XR / 4), r = e % (XR / 4), tap = r / (GPW * QL), cq = r % (GPW * QL);
+      const int p = pt + i;
+      vx[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (p < pend) {
+        const int b = dv.plane.div(p), q = p - b * plane, ho = dv.row.div(q), wo = q - ho * g.Wo;
+        const int hi = ho * g.stride - g.pad + tap / 3, wi = wo * g.stride - g.pad + tap % 3;
+        if ((unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W)
+          vx[n] = *(const float4*)(x + (((size_t)b * g.H + hi) * g.W + wi) * g.C + grp0 * CG + 4 * cq);
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < LD; ++n) {
+      const int e = tid + n * T, i = e / (DR / 4), cq = e % (DR / 4), p = pt + i;
+      vd[n] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (e < ND && p < pend) vd[n] = *(const float4*)(dy + (size_t)p * g.Co + grp0 * CG + 4 * cq);
+    }
+  };
+  const int gi = tid / UG, uc = tid % UG / (K9 / 4) * CO, uk = tid % (K9 / 4) * 4;
+  float acc[CO][4];
+#pragma unroll
+  for (int c = 0; c < CO; ++c)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[c][j] = 0.f;
+  gload(p0);
+  for (int pt = p0; pt < pend; pt += PT) {
+    __syncthreads();  // the last round's sums are done with the buffers
+#pragma unroll
+    for (int n = 0; n < LX; ++n) {
+      const int e = tid + n * T, i = e / (XR / 4), r = e % (XR / 4), tap = r / (GPW * QL), cq = r % (GPW * QL);
+      const float4 v = vx[n];
+      *(float4*)(xs + i * XR + cq / QL * K9 + tap * CG + cq % QL * 4) =
+          make_float4(opnd<BF>(v.x), opnd<BF>(v.y), opnd<BF>(v.z), opnd<BF>(v.w));
+    }
+#pragma unroll
+    for (int n = 0; n < LD; ++n)
+      if (tid + n * T < ND) *(float4*)(ds + 4 * (tid + n * T)) = vd[n];
+    __syncthreads();
+    if (pt + PT < pend) gload(pt + PT);
+    if (tid < U) {
+      const int np = min(PT, pend - pt);
+#pragma unroll 4
+      for (int i = 0; i < np; ++i) {
+        float f[4], d[CO];
+        ld4(xs + i * XR + gi * K9 + uk, f);
+#pragma unroll
+        for (int c = 0; c < CO; ++c) d[c] = ds[i * DR + gi * CG + uc + c];
+#pragma unroll
+        for (int c = 0; c < CO; ++c)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[c][j] = fmaf(d[c], f[j], acc[c][j]);
+      }
+    }
+  }
+  if (tid >= U) return;
+  float* out = part + (size_t)blockIdx.x * g.Co * K9 + (size_t)(grp0 + gi) * NE + uk;
+#pragma unroll
+  for (int c = 0; c < CO; ++c)
+    *(float4*)(out + (uc + c) * K9) = make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
+}
+
 // dst[i] = sum over chunks z (in order) of part[z][i]
 __global__ void __launch_bounds__(kThreads) chunk_sum_kernel(const float* __restrict__ part, int chunks, int n,
                                                             float* __restrict__ dst) {
   for (int i = blockIdx.x * kThreads + threadIdx.x; i < n; i += gridDim.x * kThreads) {
+    // 16 loads in flight, added in order
     float s = 0.f;
-    for (int z = 0; z < chunks; ++z) s += part[(size_t)z * n + i];
+    int z = 0;
+    for (; z + 16 <= chunks; z += 16) {
+      float v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[q] = part[(size_t)(z + q) * n + i];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) s += v[q];
+    }
+    for (; z < chunks; ++z) s += part[(size_t)z * n + i];
     dst[i] = s;
   }
 }
@@ -460,24 +643,36 @@ __global__ void __launch_bounds__(kThreads) se_fc_wgrad_kernel(const float* __re
                                                               float* __restrict__ gw1, float* __restrict__ gb1,
                                                               float* __restrict__ gw2, float* __restrict__ gb2) {
   const int n1 = R * C, n2 = n1 + R, n3 = n2 + C * R, n4 = n3 + C;
-  for (int e = blockIdx.x * kThreads + threadIdx.x; e < n4; e += gridDim.x * kThreads) {
+  // sum over the frames in order of term(f), 16 frames' loads in flight
+  auto sum = [&](auto load, auto add) {
     float acc = 0.f;
+    int f = 0;
+    for (; f + 16 <= F; f += 16) {
+      float2 v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[q] = load(f + q);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc = add(v[q], acc);
+    }
+    for (; f < F; ++f) acc = add(load(f), acc);
+    return acc;
+  };
+  auto prod = [](float2 v, float acc) { return fmaf(v.x, v.y, acc); };
+  auto plain = [](float2 v, float acc) { return acc + v.x; };
+  for (int e = blockIdx.x * kThreads + threadIdx.x; e < n4; e += gridDim.x * kThreads) {
     if (e < n1) {
       const int j = e / C, c = e - j * C;
-      for (int f = 0; f < F; ++f) acc = fmaf(da1[(size_t)f * R + j], z[(size_t)f * C + c], acc);
-      gw1[e] = acc;
+      gw1[e] = sum([=](int f) { return make_float2(da1[(size_t)f * R + j], z[(size_t)f * C + c]); }, prod);
     } else if (e < n2) {
       const int j = e - n1;
-      for (int f = 0; f < F; ++f) acc += da1[(size_t)f * R + j];
-      gb1[j] = acc;
+      gb1[j] = sum([=](int f) { return make_float2(da1[(size_t)f * R + j], 0.f); }, plain);
     } else if (e < n3) {
       const int q = e - n2, c = q / R, j = q - c * R;
-      for (int f = 0; f < F; ++f) acc = fmaf(da2[(size_t)f * C + c], fmaxf(a1[(size_t)f * R + j], 0.f), acc);
-      gw2[q] = acc;
+      gw2[q] = sum([=](int f) { return make_float2(da2[(size_t)f * C + c], fmaxf(a1[(size_t)f * R + j], 0.f)); },
+                   prod);
     } else {
       const int c = e - n3;
-      for (int f = 0; f < F; ++f) acc += da2[(size_t)f * C + c];
-      gb2[c] = acc;
+      gb2[c] = sum([=](int f) { return make_float2(da2[(size_t)f * C + c], 0.f); }, plain);
     }
   }
 }
@@ -517,27 +712,57 @@ int se_slices(int F, int HW, int C) {
   return std::min(S, kSeMaxSlices);
 }
 
-template <typename TW>
-void gconv_fwd_dispatch(int cg, dim3 grid, size_t sh, hipStream_t s, const float* x, const TW* w, float* y,
-                        const ConvGeo& g, int G, int pix, PixDiv dv) {
+// Register-tiled kernels for these groups?  (Equal input and output widths, one of the instantiated.)
+bool gconv_tiled(int cg, int og) { return cg == og && (cg == 4 || cg == 8 || cg == 16 || cg == 32); }
+
+template <typename TW, bool BWD>
+void gconv_tile(const ConvGeo& g, int G, const float* src, const TW* w, float* dst, int accumulate, hipStream_t s) {
+  const int cg = g.C / G;
+  // neighbouring groups of a workgroup: up to 16 channels, a power of two that divides the group count
+  int gpw = 1;
+  while (2 * gpw * cg <= 16 && G % (2 * gpw) == 0) gpw *= 2;
+  const int rows = kThreads / (gpw * cg / 4), H = BWD ? g.H : g.Ho, W = BWD ? g.W : g.Wo;
+  const long P = (long)g.B * H * W;
+  const int np = P * (G / gpw) >= 2L * rows * 2048 ? 2 : 1;
+  const int pix = pix_per_block(P, np * rows, G / gpw);
+  const dim3 grid((unsigned)cdiv(P, pix), (unsigned)(G / gpw));
+  const size_t sh = (size_t)gpw * (9 * cg * cg + 16) * sizeof(float);
+  const PixDiv dv{fast_div(H * W), fast_div(W)};
   switch (cg) {
-    case 4: hipLaunchKernelGGL((gconv_fwd_kernel<TW, 4>), grid, dim3(kThreads), sh, s, x, w, y, g, G, pix, dv); break;
-    case 8: hipLaunchKernelGGL((gconv_fwd_kernel<TW, 8>), grid, dim3(kThreads), sh, s, x, w, y, g, G, pix, dv); break;
-    case 16: hipLaunchKernelGGL((gconv_fwd_kernel<TW, 16>), grid, dim3(kThreads), sh, s, x, w, y, g, G, pix, dv); break;
-    case 32: hipLaunchKernelGGL((gconv_fwd_kernel<TW, 32>), grid, dim3(kThreads), sh, s, x, w, y, g, G, pix, dv); break;
-    default: hipLaunchKernelGGL((gconv_fwd_kernel<TW, 0>), grid, dim3(kThreads), sh, s, x, w, y, g, G, pix, dv);
+#define TILE(CG) \
+  case CG: \
+    if (np == 2) \
+      hipLaunchKernelGGL((gconv_tile_kernel<TW, CG, BWD, 2>), grid, dim3(kThreads), sh, s, src, w, dst, g, gpw, pix, \
+                         dv, accumulate); \
+    else \
+      hipLaunchKernelGGL((gconv_tile_kernel<TW, CG, BWD, 1>), grid, dim3(kThreads), sh, s, src, w, dst, g, gpw, pix, \
+                         dv, accumulate); \
+    break;
+    TILE(4) TILE(8) TILE(16) TILE(32)
+#undef TILE
   }
 }
 
-template <typename TW>
-void gconv_dgrad_dispatch(int og, dim3 grid, size_t sh, hipStream_t s, const float* dy, const TW* w, float* dx,
-                          const ConvGeo& g, int G, int pix, PixDiv dv, int acc) {
-  switch (og) {
-    case 4: hipLaunchKernelGGL((gconv_dgrad_kernel<TW, 4>), grid, dim3(kThreads), sh, s, dy, w, dx, g, G, pix, dv, acc); break;
-    case 8: hipLaunchKernelGGL((gconv_dgrad_kernel<TW, 8>), grid, dim3(kThreads), sh, s, dy, w, dx, g, G, pix, dv, acc); break;
-    case 16: hipLaunchKernelGGL((gconv_dgrad_kernel<TW, 16>), grid, dim3(kThreads), sh, s, dy, w, dx, g, G, pix, dv, acc); break;
-    case 32: hipLaunchKernelGGL((gconv_dgrad_kernel<TW, 32>), grid, dim3(kThreads), sh, s, dy, w, dx, g, G, pix, dv, acc); break;
-    default: hipLaunchKernelGGL((gconv_dgrad_kernel<TW, 0>), grid, dim3(kThreads), sh, s, dy, w, dx, g, G, pix, dv, acc);
+template <bool BF, int CG>
+bool gconv_wgrad_tile(const ConvGeo& g, int G, const float* x, const float* dy, float* part, int chunks, int pix,
+                      hipStream_t s) {
+  using W = WgradTile<CG>;
+  if (G % W::GPW) return false;
+  hipLaunchKernelGGL((gconv_wgrad_tile_kernel<BF, CG>), dim3((unsigned)chunks, (unsigned)(G / W::GPW)), dim3(W::T),
+                     0, s, x, dy, part, g, pix, PixDiv{fast_div(g.Ho * g.Wo), fast_div(g.Wo)});
+  return true;
+}
+
+// The register-tiled weight gradient; false where the general kernel has to run.
+template <bool BF>
+bool gconv_wgrad_tiled(const ConvGeo& g, int G, const float* x, const float* dy, float* part, int chunks, int pix,
+                       hipStream_t s) {
+  if (!gconv_tiled(g.C / G, g.Co / G)) return false;
+  switch (g.C / G) {
+    case 4: return gconv_wgrad_tile<BF, 4>(g, G, x, dy, part, chunks, pix, s);
+    case 8: return gconv_wgrad_tile<BF, 8>(g, G, x, dy, part, chunks, pix, s);
+    case 16: return gconv_wgrad_tile<BF, 16>(g, G, x, dy, part, chunks, pix, s);
+    default: return gconv_wgrad_tile<BF, 32>(g, G, x, dy, part, chunks, pix, s);
   }
 }
 
@@ -562,26 +787,42 @@ bool gconv_fits(const ConvGeo& g) {
 
 void launch_gconv_fwd(int prec, const ConvGeo& g, int G, const float* x, const void* w, float* y,
                       hipStream_t s) {
+  if (gconv_tiled(g.C / G, g.Co / G)) {
+    if (prec == 1) gconv_tile<bf16_t, false>(g, G, x, (const bf16_t*)w, y, 0, s);
+    else gconv_tile<float, false>(g, G, x, (const float*)w, y, 0, s);
+    return;
+  }
   const int cg = g.C / G, og = g.Co / G, rows = kThreads / og;
   const long P = (long)g.B * g.Ho * g.Wo;
   const int pix = pix_per_block(P, rows, G);
   const dim3 grid((unsigned)cdiv(P, pix), (unsigned)G);
   const size_t sh = (size_t)9 * cg * og * sizeof(float);
   const PixDiv dv{fast_div(g.Ho * g.Wo), fast_div(g.Wo)};
-  if (prec == 1) gconv_fwd_dispatch<bf16_t>(cg, grid, sh, s, x, (const bf16_t*)w, y, g, G, pix, dv);
-  else gconv_fwd_dispatch<float>(cg, grid, sh, s, x, (const float*)w, y, g, G, pix, dv);
+  if (prec == 1)
+    hipLaunchKernelGGL(gconv_fwd_kernel<bf16_t>, grid, dim3(kThreads), sh, s, x, (const bf16_t*)w, y, g, G, pix, dv);
+  else
+    hipLaunchKernelGGL(gconv_fwd_kernel<float>, grid, dim3(kThreads), sh, s, x, (const float*)w, y, g, G, pix, dv);
 }
 
 void launch_gconv_dgrad(int prec, const ConvGeo& g, int G, const float* dy, const void* w, float* dx,
                         int accumulate, hipStream_t s) {
+  if (gconv_tiled(g.C / G, g.Co / G)) {
+    if (prec == 1) gconv_tile<bf16_t, true>(g, G, dy, (const bf16_t*)w, dx, accumulate, s);
+    else gconv_tile<float, true>(g, G, dy, (const float*)w, dx, accumulate, s);
+    return;
+  }
   const int cg = g.C / G, og = g.Co / G, rows = kThreads / cg;
   const long P = (long)g.B * g.H * g.W;
   const int pix = pix_per_block(P, rows, G);
   const dim3 grid((unsigned)cdiv(P, pix), (unsigned)G);
   const size_t sh = (size_t)9 * cg * og * sizeof(float);
   const PixDiv dv{fast_div(g.H * g.W), fast_div(g.W)};
-  if (prec == 1) gconv_dgrad_dispatch<bf16_t>(og, grid, sh, s, dy, (const bf16_t*)w, dx, g, G, pix, dv, accumulate);
-  else gconv_dgrad_dispatch<float>(og, grid, sh, s, dy, (const float*)w, dx, g, G, pix, dv, accumulate);
+  if (prec == 1)
+    hipLaunchKernelGGL(gconv_dgrad_kernel<bf16_t>, grid, dim3(kThreads), sh, s, dy, (const bf16_t*)w, dx, g, G, pix,
+                       dv, accumulate);
+  else
+    hipLaunchKernelGGL(gconv_dgrad_kernel<float>, grid, dim3(kThreads), sh, s, dy, (const float*)w, dx, g, G, pix,
+                       dv, accumulate);
 }
 
 void launch_gconv_wgrad(int prec, const ConvGeo& g, int G, const float* x, const float* dy, float* dw,
@@ -601,7 +842,9 @@ void launch_gconv_wgrad(int prec, const ConvGeo& g, int G, const float* x, const
   const size_t sh = (size_t)PT * (og + 9 * cg) * sizeof(float) + (size_t)PT * 3 * sizeof(int);
   const dim3 grid((unsigned)chunks, (unsigned)G);
   const WgradDiv dv{{fast_div(g.Ho * g.Wo), fast_div(g.Wo)}, fast_div(og), fast_div(9 * cg / 4), fast_div(cg / 4)};
-  if (prec == 1)
+  if (prec == 1 ? gconv_wgrad_tiled<true>(g, G, x, dy, part, (int)chunks, (int)pix, s)
+                : gconv_wgrad_tiled<false>(g, G, x, dy, part, (int)chunks, (int)pix, s)) {
+  } else if (prec == 1)
     hipLaunchKernelGGL(gconv_wgrad_kernel<true>, grid, dim3(kThreads), sh, s, x, dy, part, g, G, (int)pix, PT, dv);
   else
     hipLaunchKernelGGL(gconv_wgrad_kernel<false>, grid, dim3(kThreads), sh, s, x, dy, part, g, G, (int)pix, PT, dv);
