@@ -232,6 +232,128 @@ struct ConvDgradProb {
   }
 };
 
+// 8 consecutive weights as stored, and their copy to an LDS row.
+template <typename TW> struct Raw8;
+template <> struct Raw8<bf16_t> { uint4 v; };
+template <> struct Raw8<float> { float4 v, w; };
+DEV void load_raw(const bf16_t* p, Raw8<bf16_t>& r) { r.v = *(const uint4*)p; }
+DEV void load_raw(const float* p, Raw8<float>& r) {
+  r.v = *(const float4*)p;
+  r.w = *(const float4*)(p + 4);
+}
+DEV void zero_raw(Raw8<bf16_t>& r) { r.v = make_uint4(0, 0, 0, 0); }
+DEV void zero_raw(Raw8<float>& r) { r.v = r.w = make_float4(0.f, 0.f, 0.f, 0.f); }
+DEV void put_raw(bf16_t* d, const Raw8<bf16_t>& r) { *(uint4*)d = r.v; }
+DEV void put_raw(float* d, const Raw8<float>& r) {
+  *(float4*)d = r.v;
+  *(float4*)(d + 4) = r.w;
+}
+
+// Forward and data gradient where a K tile lies in one tap (UNI: channels a
+// multiple of 32, weights 16-byte aligned): the tap and its offsets are scalars
+// of the tile (KT), a row adds its own, and weights go to LDS as they are
+// stored.  The general forms (other channel counts) divide once a chunk and
+// thread and convert bfloat16 weights to float and back.  Same values, same order.
+// All such products of 256 frames, bfloat16: forward 1.55 -> 1.23 ms, data
+// gradient 2.06 -> 1.70 ms; an act step of 4 envs 676 -> 642 us.
+template <typename TW>
+struct ConvFwdUProb {
+  static constexpr int kKind = 1;
+  typedef TW Weight;
+  ConvGeo g;
+  FastDiv dC, dKW, dHoWo, dWo;
+  const float* x;
+  const TW* w;
+  int M, N, K;
+  struct RA {
+    int base, h0, w0, ok;
+  };
+  struct RB {
+    const TW* p;
+    int ok;
+  };
+  struct KT {
+    int off, kh, kw, k;
+  };
+  DEV RA rowA(int m, int kc) const {
+    RA r{0, 0, 0, m < M};
+    if (r.ok) {
+      const int b = dHoWo.div(m), q = m - b * g.Ho * g.Wo;
+      const int ho = dWo.div(q), wo = q - ho * g.Wo;
+      r.h0 = ho * g.stride - g.pad;
+      r.w0 = wo * g.stride - g.pad;
+      r.base = ((b * g.H + r.h0) * g.W + r.w0) * g.C + kc;
+    }
+    return r;
+  }
+  DEV RB rowB(int n, int kc) const { return RB{w + (size_t)(n < N ? n : 0) * K + kc, n < N}; }
+  DEV KT ktile(int k0) const {
+    const int tap = dC.div(k0), kh = dKW.div(tap), kw = tap - kh * g.KW;
+    return KT{(kh * g.W + kw) * g.C + k0 - tap * g.C, kh, kw, k0};
+  }
+  DEV void a8(const RA& r, const KT& t, float v[8]) const {
+    if (r.ok && (unsigned)(r.h0 + t.kh) < (unsigned)g.H && (unsigned)(r.w0 + t.kw) < (unsigned)g.W)
+      return load8(x + (r.base + t.off), v);
+    zero8(v);
+  }
+  DEV void b8(const RB& r, const KT& t, Raw8<TW>& v) const {
+    if (r.ok) load_raw(r.p + t.k, v);
+    else zero_raw(v);
+  }
+};
+
+template <typename TW>
+struct ConvDgradUProb {
+  static constexpr int kKind = 2;
+  typedef TW Weight;
+  ConvGeo g;
+  FastDiv dCo, dNkw, dHqWq, dWq;
+  const float* dy;
+  const TW* wt;
+  int M, N, K;  // as ConvDgradProb
+  int step, rh, rw, kh0, kw0, nkw, Wq;
+  struct RA {
+    int off, th, tw, ok;
+  };
+  struct RB {
+    const TW* p;
+    int ok;
+  };
+  struct KT {
+    int co, kh, kw, w;
+  };
+  DEV RA rowA(int m, int kc) const {
+    RA r{0, 0, 0, m < M};
+    if (r.ok) {
+      const int b = dHqWq.div(m), q = m - b * (M / g.B);
+      const int hq = dWq.div(q), wq = q - hq * Wq;
+      r.off = b * g.Ho * g.Wo * g.Co + kc;
+      r.th = step * hq + rh + g.pad;
+      r.tw = step * wq + rw + g.pad;
+    }
+    return r;
+  }
+  DEV RB rowB(int n, int kc) const {
+    return RB{wt + (size_t)(n < N ? n : 0) * g.KH * g.KW * g.Co + kc, n < N};
+  }
+  DEV KT ktile(int k0) const {
+    const int t = dCo.div(k0), co = k0 - t * g.Co, ih = dNkw.div(t), iw = t - ih * nkw;
+    const int kh = kh0 + step * ih, kw = kw0 + step * iw;
+    return KT{co, kh, kw, (kh * g.KW + kw) * g.Co + co};
+  }
+  DEV void a8(const RA& r, const KT& t, float v[8]) const {
+    const int sh = g.stride == 2 ? 1 : 0;
+    const int th = r.th - t.kh, tw = r.tw - t.kw, ho = th >> sh, wo = tw >> sh;
+    if (r.ok && (unsigned)ho < (unsigned)g.Ho && (unsigned)wo < (unsigned)g.Wo)
+      return load8(dy + (r.off + (ho * g.Wo + wo) * g.Co + t.co), v);
+    zero8(v);
+  }
+  DEV void b8(const RB& r, const KT& t, Raw8<TW>& v) const {
+    if (r.ok) load_raw(r.p + t.w, v);
+    else zero_raw(v);
+  }
+};
+
 // Weight gradient: C(m = co, n = (kh,kw,ci)) = sum_r dy[r][co] * im2col(x)[r][n],
 // r = (b,ho,wo) is the reduction.  Both operands are contiguous along their
 // rows: lanes walk co (A) or n (B); 8 consecutive r per chunk.
@@ -396,25 +518,33 @@ struct DenseProb {
 // forward product); 0 for other products (GEMM launch timer's byte count).
 template <class P> struct WeightBytes { static constexpr int v = 0; };
 template <typename TW> struct WeightBytes<ConvFwdProb<TW>> { static constexpr int v = (int)sizeof(TW); };
+template <typename TW> struct WeightBytes<ConvFwdUProb<TW>> { static constexpr int v = (int)sizeof(TW); };
 
 // Is the operand contiguous along rows (so lanes should walk rows)?  QUADS:
 // units are 4 rows x 4 k (vector loads along rows, transposed in registers).
+// UNI: a K tile lies in one tap.
 template <class P> struct Layout;
 template <> struct Layout<ConvWgradQProb> {
-  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = true;
+  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = true, UNI = false;
 };
 template <typename TW> struct Layout<ConvFwdProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = false;
 };
 template <typename TW> struct Layout<ConvDgradProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = false;
+};
+template <typename TW> struct Layout<ConvFwdUProb<TW>> {
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = true;
+};
+template <typename TW> struct Layout<ConvDgradUProb<TW>> {
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = true;
 };
 template <> struct Layout<ConvWgradProb> {
-  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = false;
+  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = false, UNI = false;
 };
 template <typename A_, typename B_, bool TA, bool TB>
 struct Layout<DenseProb<A_, B_, TA, TB>> {
-  static constexpr bool A_ROWS = TA, B_ROWS = TB, QUADS = false;
+  static constexpr bool A_ROWS = TA, B_ROWS = TB, QUADS = false, UNI = false;
 };
 // Tile-table kind of a problem.
 template <class P> int kind_of(const P&) { return P::kKind; }
@@ -612,6 +742,42 @@ __global__ void __launch_bounds__(256) gemm_kernel(Prob p, Epi e, int tiles_n, i
       for (int q = 0; q < QU; ++q) {
         if (is_a(q)) put44(&sA[0][buf][uo[q]], LDK, vu[q], SPLIT ? &sA[NSPL - 1][buf][uo[q]] : (TC*)nullptr);
         else if (live(q)) put44(&sB[buf][uo[q]], LDK, vu[q], (TC*)nullptr);
+      }
+    };
+    mainloop(gload, sstore);
+  } else if constexpr (Layout<Prob>::UNI) {
+    typename Prob::RA ra[QA];
+    typename Prob::RB rb[QB];
+    float va[QA][8];
+    Raw8<typename Prob::Weight> vb[QB];
+#pragma unroll
+    for (int q = 0; q < QA; ++q) {
+      const int c = tid + 256 * q;
+      ra[q] = p.rowA(c < CA ? m0 + a_row(c) : 1 << 30, a_kc(c));
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int c = tid + 256 * q;
+      rb[q] = p.rowB(c < CB ? n0 + b_row(c) : 1 << 30, b_kc(c));
+    }
+    auto gload = [&](int k0) {
+      const auto kt = p.ktile(k0);
+#pragma unroll
+      for (int q = 0; q < QA; ++q) p.a8(ra[q], kt, va[q]);
+#pragma unroll
+      for (int q = 0; q < QB; ++q) p.b8(rb[q], kt, vb[q]);
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+      for (int q = 0; q < QA; ++q) {
+        const int c = tid + 256 * q;
+        const int o = a_row(c) * LDK + a_kc(c);
+        if (c < CA) put8(&sA[0][buf][o], va[q], SPLIT ? &sA[NSPL - 1][buf][o] : (TC*)nullptr);
+      }
+#pragma unroll
+      for (int q = 0; q < QB; ++q) {
+        const int c = tid + 256 * q;
+        if (c < CB) put_raw(&sB[buf][b_row(c) * LDK + b_kc(c)], vb[q]);
       }
     };
     mainloop(gload, sstore);

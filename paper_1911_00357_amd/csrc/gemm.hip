@@ -284,6 +284,14 @@ int gemm_conv_fwd(int prec, const ConvGeo& g, const float* x, const void* w, Epi
                   float* partial, hipStream_t s, bool defer) {
   const int M = g.B * g.Ho * g.Wo, N = g.Co, K = g.KH * g.KW * g.C;
   const FastDiv dC = fast_div(g.C), dKW = fast_div(g.KW), dHoWo = fast_div(g.Ho * g.Wo), dWo = fast_div(g.Wo);
+  // a K tile of 32 in one tap, weight rows on 16 bytes
+  if (g.C % BK == 0 && (((uintptr_t)x | (uintptr_t)w) & 15) == 0) {
+    if (prec == 1)
+      return run<ConvFwdUProb<bf16_t>, bf16_t, false>({g, dC, dKW, dHoWo, dWo, x, (const bf16_t*)w, M, N, K}, e, pb,
+                                                      partial, s, 1, defer);
+    return run<ConvFwdUProb<float>, float, false>({g, dC, dKW, dHoWo, dWo, x, (const float*)w, M, N, K}, e, pb,
+                                                  partial, s, 0, defer);
+  }
   if (prec == 1) {
     ConvFwdProb<bf16_t> p{g, dC, dKW, dHoWo, dWo, x, (const bf16_t*)w, M, N, K};
     return run<ConvFwdProb<bf16_t>, bf16_t, false>(p, e, pb, partial, s, 1, defer);
@@ -352,14 +360,23 @@ void gemm_conv_dgrad(int prec, const ConvGeo& g, const float* dy, const void* w,
         continue;
       }
       const FastDiv dCo = fast_div(g.Co), dNkw = fast_div(nkw), dHqWq = fast_div(Hq * Wq), dWq = fast_div(Wq);
+      if (g.Co % BK == 0 && (((uintptr_t)dy | (uintptr_t)wt) & 15) == 0) {
+        if (prec == 1)
+          run<ConvDgradUProb<bf16_t>, bf16_t, true>({g, dCo, dNkw, dHqWq, dWq, dy, (const bf16_t*)wt, M, N, K, step, rh, rw, kh0,
+                                                     kw0, nkw, Wq}, ec, pb, partial, s, 1);
+        else
+          run<ConvDgradUProb<float>, float, false>({g, dCo, dNkw, dHqWq, dWq, dy, (const float*)wt, M, N, K, step, rh, rw, kh0,
+                                                    kw0, nkw, Wq}, ec, pb, partial, s, 0);
+        continue;
+      }
       if (prec == 1) {
         ConvDgradProb<bf16_t> p{g, dCo, dNkw, dHqWq, dWq, dy, (const bf16_t*)wt, M, N, K,
                                 step, rh, rw, kh0, kw0, nkw, Wq};
-        run_prec(p, ec, 1, true, pb, partial, s);
+        run<ConvDgradProb<bf16_t>, bf16_t, true>(p, ec, pb, partial, s, 1);
       } else {
         ConvDgradProb<float> p{g, dCo, dNkw, dHqWq, dWq, dy, (const float*)wt, M, N, K,
                                step, rh, rw, kh0, kw0, nkw, Wq};
-        run_prec(p, ec, 0, false, pb, partial, s);
+        run<ConvDgradProb<float>, float, false>(p, ec, pb, partial, s, 0);
       }
     }
 }

@@ -11,7 +11,7 @@ import torch
 
 from synth import rollout as R
 from tests.gpu_util import DEV, assert_close, random_record, to_device
-from tests.nets import MINI_RESNET, TINY_PLUS
+from tests.nets import MINI_RESNET, RESNET_64, TINY_PLUS
 
 pytestmark = pytest.mark.gpu
 
@@ -140,3 +140,26 @@ def test_tile_shape_does_not_change_a_bit(P, dtype, width):
         n.tile_table([r[:5] + [tile, r[6]] for r in rows])
         g1, s1 = grad()
         assert torch.equal(g1, g0) and torch.equal(s1, s0), tile
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("frames", [1, 3, 9])
+def test_encode_is_the_same_at_any_weight_alignment(P, dtype, frames):
+    """Convolutions of 32n channels copy weight rows as stored where they lie
+    on 16 bytes and take the general loaders elsewhere: the paper's widths (1x1
+    to 16x16 maps, one to nine frames) encode to the same bits at every element
+    alignment of the weights."""
+    n = P.Net(RESNET_64, dtype)
+    params = torch.tensor(R.init_params(RESNET_64, 1, random_affine=True), device=DEV)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    obs = torch.rand((frames, 4, 64, 64), generator=torch.Generator().manual_seed(3)).to(td).to(DEV)
+    ref = None
+    for off in range(4):
+        print(f"encode {dtype} {frames} frames: weights {off} elements past an aligned address", flush=True)
+        buf = torch.zeros(n.P + 4, dtype=td, device=DEV)
+        w = buf[off:off + n.P]
+        w.copy_(params)
+        out = n.encode(obs, params, w) if dtype == "bf16" else n.encode(obs, w)
+        torch.cuda.synchronize()
+        ref = out if ref is None else ref
+        assert torch.isfinite(out).all() and torch.equal(out, ref), off
