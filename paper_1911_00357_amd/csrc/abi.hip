@@ -563,9 +563,11 @@ void gn_bwd(const Ctx& c, int ui, const float* dout, const float* mask_out, bool
                      c.pf(u.g), du, dres, c.grad + u.g, c.grad + u.b, c.at<float2>(c.w->gbpart), c.s);
     return;
   }
-  launch_gn_backward(dout, mask_out, chw ? 1 : 0, c.at(c.w->u[ui]), c.F, P, u.Cout, G, c.at<float2>(c.w->st[ui]),
-                     c.pf(u.g), du, dres, c.grad + u.g, c.grad + u.b, c.at<float2>(c.w->gbpart),
-                     c.at<float2>(c.w->gcoef), u.S, c.s);
+  // a unit with a residual (dres) is masked by its saved output, others by their recomputed one
+  const GnMask mask = !mask_out ? GnMask::none : dres ? GnMask::out : gn_one_launch(c, u) ? GnMask::fused : GnMask::apply;
+  launch_gn_backward(dout, mask_out, mask, chw ? 1 : 0, c.at(c.w->u[ui]), c.F, P, u.Cout, G,
+                     c.at<float2>(c.w->st[ui]), c.pf(u.g), c.pf(u.b), du, dres, c.grad + u.g, c.grad + u.b,
+                     c.at<float2>(c.w->gbpart), c.at<float2>(c.w->gcoef), u.S, c.s);
 }
 
 void unit_bwd(const Ctx& c, int ui, const float* dout, const float* mask_out, bool chw, const float* x,

@@ -121,9 +121,14 @@ void gemm_dense(int prec, bool ta, bool tb, const float* a, int lda, const void*
 void launch_gn_forward(const float* y, int B, int P, int C, int G, float eps, const float* gamma,
                        const float* beta, const float* res, int relu, float* out, int out_chw,
                        float2* stats, float4* part, int S, hipStream_t s);
-void launch_gn_backward(const float* dout, const float* out, int chw, const float* y, int B, int P,
-                        int C, int G, const float2* stats, const float* gamma, float* dy, float* dres,
-                        float* dgamma, float* dbeta, float2* bpart, float2* coef, int S, hipStream_t s);
+// Where a GroupNorm backward takes its ReLU mask from: no mask, the saved
+// output, or the output formed again from y as launch_gn_forward (apply) or
+// launch_gn_fused (fused) formed it (no residual, plain ReLU).
+enum class GnMask { none, out, apply, fused };
+void launch_gn_backward(const float* dout, const float* out, GnMask mask, int chw, const float* y, int B, int P,
+                        int C, int G, const float2* stats, const float* gamma, const float* beta, float* dy,
+                        float* dres, float* dgamma, float* dbeta, float2* bpart, float2* coef, int S,
+                        hipStream_t s);
 void launch_maxpool_fwd(const float* x, int B, int H, int W, int C, float* y, uint8_t* arg,
                         hipStream_t s);
 void launch_maxpool_bwd(const float* dy, const uint8_t* arg, int B, int H, int W, int C, float* dx,

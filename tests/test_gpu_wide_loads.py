@@ -1,6 +1,7 @@
 """The kernels that read four elements at a time, at the sizes where that can
 go wrong: frames at every element alignment, gradients with a remainder past
-the last quad, weight gradients on every tile, pooling at odd channel-quad counts, and the packing of
+the last quad, weight gradients on every tile,
+the recomputed ReLU mask at its border, pooling at odd channel-quad counts, and the packing of
 minibatches whose lengths reach every form (one env, length 1, more frames
 than a workgroup)."""
 import dataclasses
@@ -163,3 +164,39 @@ def test_encode_is_the_same_at_any_weight_alignment(P, dtype, frames):
         torch.cuda.synchronize()
         ref = out if ref is None else ref
         assert torch.isfinite(out).all() and torch.equal(out, ref), off
+
+
+@pytest.mark.parametrize("fwd", ["apply", "fused"])
+def test_recomputed_relu_mask_at_its_border(P, monkeypatch, fwd):
+    """The GroupNorm backward forms the ReLU mask again from y as the forward's
+    kernel did (three-launch or one-launch).  Channels of scale 0 put out their
+    shift at every pixel: 0, -tiny and +tiny decide the mask alone, so a channel
+    whose output is not positive has gradients of exactly 0 and one at +tiny
+    has not.  Float32; the whole gradient against the one-launch backward, which
+    masks by the saved output (other orders of float32 sums)."""
+    print(f"recomputed mask, forward {fwd}", flush=True)
+    net = dataclasses.replace(MINI_RESNET, base_width=12)
+    rec, envs, lengths = random_record(net, 3, 3, 5, lengths=[3, 2, 2]), [0, 1, 2], [3, 2, 2]
+    n = P.Net(net, "f32")
+    off = {nm: (o, c) for nm, o, c in n.tensors()}
+    flat = np.array(R.init_params(net, 6, random_affine=True))
+    units = [nm[:-5] for nm in off if nm.endswith(".gn.g") and (nm.endswith("c1.gn.g") or nm.endswith("c2.gn.g"))]
+    tiny = np.float32(1e-30)
+    for u in units:
+        g, b = off[u + ".gn.g"][0], off[u + ".gn.b"][0]
+        flat[g:g + 3] = 0.0
+        flat[b:b + 3] = (0.0, -tiny, tiny)
+    params, ro = torch.tensor(flat, device=DEV), to_device(rec)
+
+    def grad(bwd_max):
+        monkeypatch.setenv("DDPPO_GN_FUSED_MAX", "0" if fwd == "apply" else str(1 << 30))
+        monkeypatch.setenv("DDPPO_GNB_FUSED_MAX", str(bwd_max))
+        g, _ = n.loss_backward(ro, envs, lengths, params, None, P.LossCfg())
+        torch.cuda.synchronize()
+        return g.cpu().numpy().astype(np.float64)
+
+    got, ref = grad(0), grad(1 << 30)
+    for u in units:
+        b = off[u + ".gn.b"][0]
+        assert got[b] == 0 and got[b + 1] == 0 and got[b + 2] != 0, (u, got[b:b + 3])
+    assert_close("gradient", got, ref, 1e-5)
