@@ -89,13 +89,21 @@ int splits_for(long tiles, long K) {
 // The tile that is launched, given the one the K split was chosen for: the
 // split, and with it every sum, does not depend on it.  Times are of 256
 // frames, one product, in us.
-Tile launch_tile_of(Tile t, long M, long N, long K, int prec, bool quads) {
+Tile launch_tile_of(Tile t, long M, long N, long K, int splits, int prec, bool quads) {
   // Channel quads: a 64x64 tile gives every thread one unit and more workgroups
   // than the wider or narrower tiles, some of whose threads idle (bfloat16:
   // 128 x 32 products 74 -> 55, 32 x 128 ones 86 -> 49).  Not for float32 rows
   // of which a 64-row tile pads half: those are bound by the matrix cores
   // (32 x 288: 145 against 113).
   if (quads) return t == T128x128 || (prec == 0 && M <= 32 && N > 128) ? t : T64x64;
+  // A grid that leaves CUs idle takes the smaller tile, for twice the workgroups.
+  // An act step of 4 envs, all products of that size, us of the whole step:
+  // 64 rows by 256 and 1024 columns (stage 3) bfloat16 -22, float32 -27; float32
+  // 1024 and 4096 rows by 64 columns (stage 1) -21.  Grids past 256 workgroups
+  // lose by it in float32 (65536 x 64 x 576, 512 workgroups: 67 to 80 us).
+  if ((t == T64x128 || t == T128x64) &&
+      (long)cdiv(M, dim_of(t).bm) * cdiv(N, dim_of(t).bn) * splits < 256)
+    return T64x64;
   // Others: with few K tiles a workgroup is mostly its first loads and its
   // stores, and smaller tiles keep more of them in flight per CU (LDS 25 KB
   // against 60).  bfloat16, M x N x K:
@@ -243,7 +251,7 @@ int run(const Prob& p, Epi e, size_t partial_bytes, float* partial, hipStream_t 
   const bool act = e.act && defer;
   const int min_split = act ? (int)std::max<long>(1, std::min<long>({4L, (long)p.K / 64, cap})) : 1;
   splits = std::max(splits, min_split);
-  t = launch_tile_of(t, p.M, p.N, p.K, prec, Layout<Prob>::QUADS);
+  t = launch_tile_of(t, p.M, p.N, p.K, splits, prec, Layout<Prob>::QUADS);
   GemmTune* tu = g_gemm_tune;
   if (tu) {
     // a deferred product (its partial tiles summed by the consumer) is tuned
