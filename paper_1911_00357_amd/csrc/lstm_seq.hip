@@ -26,6 +26,13 @@
 // sets the error word and writes NaN into its remaining outputs, so the
 // kernel always ends and the failure shows as a non-finite loss or gradient.
 //
+// A step is a chain of latencies (arrival, the slowest block, the exchanged
+// rows, the dot products, the cells), so the two-layer kernels keep everything
+// else off it: stores that no block reads in the launch leave after the
+// arrival, the next step's own inputs are loaded before the wait, and the
+// second layer's cells run on another wavefront.  4 envs, 128 steps, 512
+// units: forward 890 -> 799 us, backward 1267 -> 994 us.
+//
 // Packed rows: envs are ordered longest first, so step t covers rows
 // [off[t], off[t] + act[t]) with act[t] = #{j : len_j > t} and
 // off[t] = sum_j min(len_j, t); row r of step t is the minibatch's env r.
@@ -125,12 +132,18 @@ constexpr int kFlagStride = 64;  // words: one 256-byte line per block
 // visible until the next learner call clears it (launch_lstm_clear_error).
 constexpr int kErrWord = kFlagStride * 256;
 
-// Barrier `gen` (1, 2, ...) of the launch; `broken` is uniform in the block.
-DEV void grid_sync(unsigned* flags, unsigned gen, int& broken) {
+// Barrier `gen` (1, 2, ...) of the launch, in two halves: a block publishes its
+// arrival once its wavefronts' exchange stores are acknowledged, and waits for
+// the others.  Work between the halves (stores that no block reads in the
+// launch, loads of the next step's own inputs) overlaps the wait.
+DEV void grid_arrive(unsigned* flags, unsigned gen) {
   __builtin_amdgcn_s_waitcnt(0);  // this wavefront's exchange stores are acknowledged
   __syncthreads();
   if (threadIdx.x == 0)
     __hip_atomic_store(flags + kFlagStride * blockIdx.x, gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// `broken` is uniform in the block.
+DEV void grid_wait(unsigned* flags, unsigned gen, int& broken) {
   if (broken) return;
   for (int spins = 0;; ++spins) {
     unsigned v = gen;
@@ -145,6 +158,10 @@ DEV void grid_sync(unsigned* flags, unsigned gen, int& broken) {
     }
     __builtin_amdgcn_s_sleep(1);
   }
+}
+DEV void grid_sync(unsigned* flags, unsigned gen, int& broken) {
+  grid_arrive(flags, gen);
+  grid_wait(flags, gen, broken);
 }
 
 // off[t] for t in [0, TB] into LDS.
@@ -395,12 +412,31 @@ __global__ void __launch_bounds__(256) lstm_seq2_fwd_kernel(Seq2Args a) {
   }
   const rsrc_t rHP0 = xrsrc(a.HP0), rHo0 = xrsrc(a.Ho0), rHP1 = xrsrc(a.HP1);
   packed_offsets(a.len, a.nb, a.TB, off);
+  // pointwise items (row, unit): layer 0's of thread tid, layer 1's of another
+  // wavefront where both fit, so that the two run side by side
   const int pr = threadIdx.x / U, pu = threadIdx.x % U, pj = j0 + pu;
+  const int tid1 = (threadIdx.x + (a.nb * U <= 128 ? 128 : 0)) & 255;
+  const int qr = tid1 / U, qu = tid1 % U, qj = j0 + qu;
   __syncthreads();
   if (pr < off[1]) {
     c0s[pr * U + pu] = a.CP0[(size_t)pr * H + pj];
     c1s[pr * U + pu] = a.CP1[(size_t)pr * H + pj];
   }
+  // inputs of this thread's items at step k that no block writes in the launch:
+  // fetched while the block waits for the others
+  float gin[4] = {0.f, 0.f, 0.f, 0.f}, bias1[4], mn0 = 0.f, mn1 = 0.f;
+#pragma unroll
+  for (int qq = 0; qq < 4; ++qq) bias1[qq] = a.b1[qq * H + qj];
+  auto fetch = [&](int k) {
+    if (k < a.TB && pr < off[k + 1] - off[k]) {
+      const float* g = a.G0 + (size_t)(off[k] + pr) * 4 * H + pj;
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) gin[qq] = g[qq * H];
+      if (k + 1 < a.TB && pr < off[k + 2] - off[k + 1]) mn0 = a.mskf[off[k + 1] + pr];
+    }
+    if (k >= 1 && k < a.TB && qr < off[k + 1] - off[k]) mn1 = a.mskf[off[k] + qr];
+  };
+  fetch(0);
   __syncthreads();
   for (int k = 0; k <= a.TB; ++k) {
     const bool l0 = k < a.TB, l1 = k >= 1;
@@ -409,19 +445,6 @@ __global__ void __launch_bounds__(256) lstm_seq2_fwd_kernel(Seq2Args a) {
     const int nb0 = l0 ? off[t0 + 1] : 0, nrows0 = (l0 && t0 + 1 < a.TB) ? off[t0 + 2] - nb0 : 0;
     const int base1 = l1 ? off[t1] : 0, rows1 = l1 ? off[t1 + 1] - base1 : 0;
     const int nb1 = l1 ? off[t1 + 1] : 0, nrows1 = (l1 && t1 + 1 < a.TB) ? off[t1 + 2] - nb1 : 0;
-    // pointwise inputs of this thread's items (layer 0 and layer 1, row pr)
-    float gin[4] = {0.f, 0.f, 0.f, 0.f}, bias1[4] = {0.f, 0.f, 0.f, 0.f}, mn0 = 0.f, mn1 = 0.f;
-    if (pr < rows0) {
-      const float* g = a.G0 + (size_t)(base0 + pr) * 4 * H + pj;
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq) gin[qq] = g[qq * H];
-      if (pr < nrows0) mn0 = a.mskf[nb0 + pr];
-    }
-    if (pr < rows1) {
-#pragma unroll
-      for (int qq = 0; qq < 4; ++qq) bias1[qq] = a.b1[qq * H + pj];
-      if (pr < nrows1) mn1 = a.mskf[nb1 + pr];
-    }
     // layer 0: m h_{k-1} W_hh0^T; layer 1: h0_{k-1} W_ih1^T + m h1_{k-2} W_hh1^T
     const int rmax = max(rows0, rows1);
     for (int c0 = 0; c0 < rmax; c0 += kRowsF2) {
@@ -451,47 +474,56 @@ __global__ void __launch_bounds__(256) lstm_seq2_fwd_kernel(Seq2Args a) {
       __syncthreads();
     }
     const float nan = broken ? __builtin_nanf("") : 1.f;
+    // cells of both layers; the rows that other blocks read leave first
+    float ac0[5], ac1[5], h1 = 0.f;  // i, f, g, o, c
     if (pr < rows0) {
       const float* gr = g0 + pr * 4 * U + pu;
       const float ig = sigm(gr[0] + gin[0]), fg = sigm(gr[U] + gin[1]);
       const float gg = tanhf(gr[2 * U] + gin[2]), og = sigm(gr[3 * U] + gin[3]);
       const float c2 = fg * c0s[pr * U + pu] + ig * gg;
       const float h2 = nan * og * tanhf(c2);
-      const size_t row = base0 + pr;
-      float* ga = a.G0 + row * 4 * H + pj;
-      ga[0] = ig;
-      ga[H] = fg;
-      ga[2 * H] = gg;
-      ga[3 * H] = og;
-      a.Cs0[row * H + pj] = c2;
-      xstore(a.Ho0 + row * H + pj, h2);
-      if (pr < nrows0) {
-        xstore(a.HP0 + (size_t)(nb0 + pr) * H + pj, mn0 * h2);
-        a.CP0[(size_t)(nb0 + pr) * H + pj] = mn0 * c2;
-        c0s[pr * U + pu] = mn0 * c2;
-      }
+      ac0[0] = ig; ac0[1] = fg; ac0[2] = gg; ac0[3] = og; ac0[4] = c2;
+      xstore(a.Ho0 + (size_t)(base0 + pr) * H + pj, h2);
+      if (pr < nrows0) xstore(a.HP0 + (size_t)(nb0 + pr) * H + pj, mn0 * h2);
     }
-    if (pr < rows1) {
-      const float* gr = g1 + pr * 4 * U + pu;
+    if (qr < rows1) {
+      const float* gr = g1 + qr * 4 * U + qu;
       const float ig = sigm(gr[0] + bias1[0]), fg = sigm(gr[U] + bias1[1]);
       const float gg = tanhf(gr[2 * U] + bias1[2]), og = sigm(gr[3 * U] + bias1[3]);
-      const float c2 = fg * c1s[pr * U + pu] + ig * gg;
-      const float h2 = nan * og * tanhf(c2);
-      const size_t row = base1 + pr;
-      float* ga = a.G1 + row * 4 * H + pj;
-      ga[0] = ig;
-      ga[H] = fg;
-      ga[2 * H] = gg;
-      ga[3 * H] = og;
-      a.Cs1[row * H + pj] = c2;
-      a.Ho1[row * H + pj] = h2;
-      if (pr < nrows1) {
-        xstore(a.HP1 + (size_t)(nb1 + pr) * H + pj, mn1 * h2);
-        a.CP1[(size_t)(nb1 + pr) * H + pj] = mn1 * c2;
-        c1s[pr * U + pu] = mn1 * c2;
+      const float c2 = fg * c1s[qr * U + qu] + ig * gg;
+      h1 = nan * og * tanhf(c2);
+      ac1[0] = ig; ac1[1] = fg; ac1[2] = gg; ac1[3] = og; ac1[4] = c2;
+      if (qr < nrows1) xstore(a.HP1 + (size_t)(nb1 + qr) * H + qj, mn1 * h1);
+    }
+    if (k < a.TB) grid_arrive(a.sync, (unsigned)(k + 1));
+    // what only later launches read
+    if (pr < rows0) {
+      const size_t row = base0 + pr;
+      float* ga = a.G0 + row * 4 * H + pj;
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) ga[qq * H] = ac0[qq];
+      a.Cs0[row * H + pj] = ac0[4];
+      if (pr < nrows0) {
+        a.CP0[(size_t)(nb0 + pr) * H + pj] = mn0 * ac0[4];
+        c0s[pr * U + pu] = mn0 * ac0[4];
       }
     }
-    if (k < a.TB) grid_sync(a.sync, (unsigned)(k + 1), broken);
+    if (qr < rows1) {
+      const size_t row = base1 + qr;
+      float* ga = a.G1 + row * 4 * H + qj;
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) ga[qq * H] = ac1[qq];
+      a.Cs1[row * H + qj] = ac1[4];
+      a.Ho1[row * H + qj] = h1;
+      if (qr < nrows1) {
+        a.CP1[(size_t)(nb1 + qr) * H + qj] = mn1 * ac1[4];
+        c1s[qr * U + qu] = mn1 * ac1[4];
+      }
+    }
+    if (k < a.TB) {
+      fetch(k + 1);
+      grid_wait(a.sync, (unsigned)(k + 1), broken);
+    }
   }
 }
 
@@ -530,26 +562,57 @@ __global__ void __launch_bounds__(256) lstm_seq2_bwd_kernel(Seq2Args a) {
   }
   const rsrc_t rdG1 = xrsrc(a.dG1), rdG0 = xrsrc(a.dG0);
   packed_offsets(a.len, a.nb, a.TB, off);
+  // pointwise items as in the forward: layer 0's (pr, pu), layer 1's (qr, qu)
   const int pr = threadIdx.x / U, pu = threadIdx.x % U, pj = j0 + pu;
+  const int tid1 = (threadIdx.x + (a.nb * U <= 128 ? 128 : 0)) & 255;
+  const int qr = tid1 / U, qu = tid1 % U, qj = j0 + qu;
   if (pr < a.nb) {
     d1s[pr * U + pu] = 0.f;
     d0s[pr * U + pu] = 0.f;
   }
   __syncthreads();
-  auto cell_bwd = [&](const float* G, const float* Cs, const float* CP, size_t row, float dh, float dc,
-                      float* dG, float nan) -> float {
-    const float* gp = G + row * 4 * H + pj;
-    const float ig = gp[0], fg = gp[H], gg = gp[2 * H], og = gp[3 * H];
-    const float tc = tanhf(Cs[row * H + pj]);
+  // a cell's saved values (written by earlier launches), fetched while the
+  // block waits for the others
+  struct Cell {
+    float ig, fg, gg, og, cs, cp, m;
+  };
+  Cell cl0{}, cl1{};
+  float dht = 0.f;
+  auto load_cell = [&](const float* G, const float* Cs, const float* CP, size_t row, int j, Cell& c) {
+    const float* gp = G + row * 4 * H + j;
+    c.ig = gp[0];
+    c.fg = gp[H];
+    c.gg = gp[2 * H];
+    c.og = gp[3 * H];
+    c.cs = Cs[row * H + j];
+    c.cp = CP[row * H + j];
+  };
+  auto fetch = [&](int k) {
+    const int t1 = a.TB - 1 - k, t0 = a.TB - k;
+    if (t1 >= 0 && qr < off[t1 + 1] - off[t1]) {
+      const size_t row = off[t1] + qr;
+      load_cell(a.G1, a.Cs1, a.CP1, row, qj, cl1);
+      dht = a.dHtop[row * H + qj];
+      if (t0 < a.TB && qr < off[t0 + 1] - off[t0]) cl1.m = a.mskf[off[t0] + qr];
+    }
+    if (k >= 1 && pr < off[t0 + 1] - off[t0]) {
+      load_cell(a.G0, a.Cs0, a.CP0, off[t0] + pr, pj, cl0);
+      if (t0 + 1 < a.TB && pr < off[t0 + 2] - off[t0 + 1]) cl0.m = a.mskf[off[t0 + 1] + pr];
+    }
+  };
+  auto cell_bwd = [&](const Cell& c, size_t row, int j, float dh, float dc, float* dG, float nan) -> float {
+    const float ig = c.ig, fg = c.fg, gg = c.gg, og = c.og;
+    const float tc = tanhf(c.cs);
     const float d_o = dh * tc;
     dc += dh * og * (1.f - tc * tc);
-    float* d = dG + row * 4 * H + pj;
+    float* d = dG + row * 4 * H + j;
     xstore(d, nan * (dc * gg * ig * (1.f - ig)));
-    xstore(d + H, nan * (dc * CP[row * H + pj] * fg * (1.f - fg)));
+    xstore(d + H, nan * (dc * c.cp * fg * (1.f - fg)));
     xstore(d + 2 * H, nan * (dc * ig * (1.f - gg * gg)));
     xstore(d + 3 * H, nan * (d_o * og * (1.f - og)));
     return dc * fg;
   };
+  fetch(0);
   for (int k = 0; k <= a.TB; ++k) {
     const int t1 = a.TB - 1 - k, t0 = a.TB - k;  // layer 1 step, layer 0 step
     const bool l1 = t1 >= 0, l0 = k >= 1;
@@ -580,37 +643,41 @@ __global__ void __launch_bounds__(256) lstm_seq2_bwd_kernel(Seq2Args a) {
       __syncthreads();
     }
     const float nan = broken ? __builtin_nanf("") : 1.f;
-    auto wsum = [&](const float* red, int r) {
+    auto wsum = [&](const float* red, int r, int u) {
       float v = 0.f;
 #pragma unroll
-      for (int q = 0; q < WPU; ++q) v += red[(pu * WPU + q) * kMaxMbEnvs + r];
+      for (int q = 0; q < WPU; ++q) v += red[(u * WPU + q) * kMaxMbEnvs + r];
       return v;
     };
     if (l1) {
       const int b1r = off[t1], n1 = off[t1 + 1] - b1r;
-      if (pr < n1) {
-        float dh = a.dHtop[(size_t)(b1r + pr) * H + pj], dc = 0.f;
-        if (pr < re) {
-          const float m = a.mskf[be + pr];
-          dh += m * wsum(r1, pr);
-          dc = m * d1s[pr * U + pu];
+      if (qr < n1) {
+        float dh = dht, dc = 0.f;
+        if (qr < re) {
+          const float m = cl1.m;
+          dh += m * wsum(r1, qr, qu);
+          dc = m * d1s[qr * U + qu];
         }
-        d1s[pr * U + pu] = cell_bwd(a.G1, a.Cs1, a.CP1, b1r + pr, dh, dc, a.dG1, nan);
+        d1s[qr * U + qu] = cell_bwd(cl1, b1r + qr, qj, dh, dc, a.dG1, nan);
       }
     }
     if (l0) {
       const int b0r = off[t0], n0 = off[t0 + 1] - b0r;
       if (pr < n0) {
-        float dh = wsum(rx, pr), dc = 0.f;
+        float dh = wsum(rx, pr, pu), dc = 0.f;
         if (pr < rd) {
-          const float m = a.mskf[bd + pr];
-          dh += m * wsum(r0, pr);
+          const float m = cl0.m;
+          dh += m * wsum(r0, pr, pu);
           dc = m * d0s[pr * U + pu];
         }
-        d0s[pr * U + pu] = cell_bwd(a.G0, a.Cs0, a.CP0, b0r + pr, dh, dc, a.dG0, nan);
+        d0s[pr * U + pu] = cell_bwd(cl0, b0r + pr, pj, dh, dc, a.dG0, nan);
       }
     }
-    if (k < a.TB) grid_sync(a.sync, (unsigned)(k + 1), broken);
+    if (k < a.TB) {
+      grid_arrive(a.sync, (unsigned)(k + 1));
+      fetch(k + 1);
+      grid_wait(a.sync, (unsigned)(k + 1), broken);
+    }
   }
 }
 
