@@ -31,7 +31,7 @@
 // else off it: stores that no block reads in the launch leave after the
 // arrival, the next step's own inputs are loaded before the wait, and the
 // second layer's cells run on another wavefront.  4 envs, 128 steps, 512
-// units: forward 890 -> 799 us, backward 1267 -> 994 us.
+// units: forward 890 -> 799 us, backward 1267 -> 994 us; with lane_sum 717 and 695.
 //
 // Packed rows: envs are ordered longest first, so step t covers rows
 // [off[t], off[t] + act[t]) with act[t] = #{j : len_j > t} and
@@ -124,6 +124,33 @@ DEV float ldot(const float* row, int s, const float (&w)[KPT]) {
     acc = fmaf(v.w, w[4 * i + 3], acc);
   }
   return acc;
+}
+
+// Sum over the T lanes (16, 32 or 64, aligned) a dot product is spread over, in
+// every lane: the butterfly lane ^ T/2, ..., lane ^ 1 in vector instructions
+// (half-wave and row swaps, then rotations of a row of 16, whose partner holds
+// the same bits as that of the xor) instead of shuffles through LDS, six of
+// which in a chain take longer than the dot product.  All lanes active.
+template <int T>
+DEV float lane_sum(float v) {
+  static_assert(T == 16 || T == 32 || T == 64, "lanes");
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  if constexpr (T >= 64) {
+    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+  }
+  if constexpr (T >= 32) {
+    const u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+  }
+#define ROR_ADD(n) \
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xf, 0xf, false))
+  ROR_ADD(8);
+  ROR_ADD(4);
+  ROR_ADD(2);
+  ROR_ADD(1);
+#undef ROR_ADD
+  return v;
 }
 
 constexpr int kFlagStride = 64;  // words: one 256-byte line per block
@@ -458,14 +485,12 @@ __global__ void __launch_bounds__(256) lstm_seq2_fwd_kernel(Seq2Args a) {
         stage<stage_nl(kRowsF2, H), 3>(src, e0, n4, dst, BF);
       }
       __syncthreads();
+#pragma unroll 2
       for (int r = 0; r < max(n0, n1); ++r) {
         float acc0 = r < n0 ? ldot<KPT, TPC>(s0 + r * H, s, w0) : 0.f;
         float acc1 = r < n1 ? ldot<KPT, TPC>(sx + r * H, s, w1i) + ldot<KPT, TPC>(s1 + r * H, s, w1h) : 0.f;
-#pragma unroll
-        for (int o = TPC / 2; o > 0; o >>= 1) {
-          acc0 += __shfl_xor(acc0, o, kWave);
-          acc1 += __shfl_xor(acc1, o, kWave);
-        }
+        acc0 = lane_sum<TPC>(acc0);
+        acc1 = lane_sum<TPC>(acc1);
         if (s == 0) {
           if (r < n0) g0[(c0 + r) * 4 * U + col] = acc0;
           if (r < n1) g1[(c0 + r) * 4 * U + col] = acc1;
@@ -630,10 +655,11 @@ __global__ void __launch_bounds__(256) lstm_seq2_bwd_kernel(Seq2Args a) {
         stage<stage_nl(kRowsB2, H4), 2>(src, e0, n4, dst, false);
       }
       __syncthreads();
+#pragma unroll 2
       for (int r = 0; r < n1; ++r) {
-        const float a1 = l1 ? wave_sum(ldot<KPT, TPB>(s1 + r * H4, s, w1h)) : 0.f;
-        const float ax = l0 ? wave_sum(ldot<KPT, TPB>(s1 + r * H4, s, w1i)) : 0.f;
-        const float a0 = r < nd ? wave_sum(ldot<KPT, TPB>(s0 + r * H4, s, w0)) : 0.f;
+        const float a1 = l1 ? lane_sum<64>(ldot<KPT, TPB>(s1 + r * H4, s, w1h)) : 0.f;
+        const float ax = l0 ? lane_sum<64>(ldot<KPT, TPB>(s1 + r * H4, s, w1i)) : 0.f;
+        const float a0 = r < nd ? lane_sum<64>(ldot<KPT, TPB>(s0 + r * H4, s, w0)) : 0.f;
         if (lane == 0) {
           r1[wave * kMaxMbEnvs + c0 + r] = a1;
           rx[wave * kMaxMbEnvs + c0 + r] = ax;
