@@ -151,8 +151,7 @@ __global__ void __launch_bounds__(256) lstm_act_layer_kernel(const float* __rest
     for (int i = 0; i < KMAX; ++i)
 #pragma unroll
       for (int e = 0; e < E; ++e) acc = fmaf(op_round(xv[i][e], BF), w[i][e], acc);
-#pragma unroll
-    for (int o = TPC / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+    acc = lane_sum<TPC>(acc);
     if (s == 0) gates[r * 4 * U + col] = acc;
 #pragma unroll
     for (int i = 0; i < KMAX; ++i)

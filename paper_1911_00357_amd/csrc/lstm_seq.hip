@@ -126,33 +126,6 @@ DEV float ldot(const float* row, int s, const float (&w)[KPT]) {
   return acc;
 }
 
-// Sum over the T lanes (16, 32 or 64, aligned) a dot product is spread over, in
-// every lane: the butterfly lane ^ T/2, ..., lane ^ 1 in vector instructions
-// (half-wave and row swaps, then rotations of a row of 16, whose partner holds
-// the same bits as that of the xor) instead of shuffles through LDS, six of
-// which in a chain take longer than the dot product.  All lanes active.
-template <int T>
-DEV float lane_sum(float v) {
-  static_assert(T == 16 || T == 32 || T == 64, "lanes");
-  typedef unsigned u2 __attribute__((ext_vector_type(2)));
-  if constexpr (T >= 64) {
-    const u2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r.x) + __uint_as_float(r.y);
-  }
-  if constexpr (T >= 32) {
-    const u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r.x) + __uint_as_float(r.y);
-  }
-#define ROR_ADD(n) \
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + (n), 0xf, 0xf, false))
-  ROR_ADD(8);
-  ROR_ADD(4);
-  ROR_ADD(2);
-  ROR_ADD(1);
-#undef ROR_ADD
-  return v;
-}
-
 constexpr int kFlagStride = 64;  // words: one 256-byte line per block
 // The error word sits on the line after the largest grid's flags (at most 256
 // blocks, pick_units); launches clear only their flags, so a failure stays
@@ -263,9 +236,7 @@ __global__ void __launch_bounds__(256) lstm_seq_fwd_kernel(SeqArgs a) {
       }
       __syncthreads();
       for (int r = 0; r < nr; ++r) {
-        float acc = ldot<KPT, TPC>(stg + r * H, s, w);
-#pragma unroll
-        for (int o = TPC / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
+        const float acc = lane_sum<TPC>(ldot<KPT, TPC>(stg + r * H, s, w));
         if (s == 0) gates[(c0 + r) * 4 * U + col] = acc;
       }
       __syncthreads();
@@ -657,9 +628,9 @@ __global__ void __launch_bounds__(256) lstm_seq2_bwd_kernel(Seq2Args a) {
       __syncthreads();
 #pragma unroll 2
       for (int r = 0; r < n1; ++r) {
-        const float a1 = l1 ? lane_sum<64>(ldot<KPT, TPB>(s1 + r * H4, s, w1h)) : 0.f;
-        const float ax = l0 ? lane_sum<64>(ldot<KPT, TPB>(s1 + r * H4, s, w1i)) : 0.f;
-        const float a0 = r < nd ? lane_sum<64>(ldot<KPT, TPB>(s0 + r * H4, s, w0)) : 0.f;
+        const float a1 = l1 ? wave_sum(ldot<KPT, TPB>(s1 + r * H4, s, w1h)) : 0.f;
+        const float ax = l0 ? wave_sum(ldot<KPT, TPB>(s1 + r * H4, s, w1i)) : 0.f;
+        const float a0 = r < nd ? wave_sum(ldot<KPT, TPB>(s0 + r * H4, s, w0)) : 0.f;
         if (lane == 0) {
           r1[wave * kMaxMbEnvs + c0 + r] = a1;
           rx[wave * kMaxMbEnvs + c0 + r] = ax;
