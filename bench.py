@@ -448,7 +448,7 @@ def cpu_baseline(wl, seed):
 
 # ------------------------------------------------------------------ roofline
 OPS = ["conv forward", "conv data gradient", "conv weight gradient"]
-ACT_KERNEL = "act-step convolution GEMMs (gemm_kernel<ConvFwdProb<bf16>, ...>, all tiles)"
+ACT_KERNEL = "act-step convolution GEMMs (gemm_kernel<ConvFwdProb / ConvFwdUProb<bf16>, ...>, all tiles)"
 
 
 def dominant_gemm(wl, seed, reps=5):
@@ -676,12 +676,12 @@ def summarize_trace(csv_path, log_path=None, ref_path=None):
         timed = rows[marks[0] + 1:marks[1]]
         gae = next(i for i, r in enumerate(timed) if r["Kernel_Name"].startswith("gae_kernel"))
         table(timed[:gae], "act loop of the timed iteration (129 act steps, one graph replay)")
-        conv = [dur(r) for r in timed[:gae] if "ConvFwdProb" in r["Kernel_Name"]]
+        conv = [dur(r) for r in timed[:gae] if "ConvFwd" in r["Kernel_Name"]]
         out.append(f"\nact convolution GEMMs in the graph replay: {len(conv)} launches, average "
                    f"{sum(conv) / max(len(conv), 1):.3f} us")
         out.extend(act_step_positions(timed[:gae], dur))
         table(timed[gae:], "update of the timed iteration")
-        after = [r for r in rows[marks[1] + 1:] if "ConvFwdProb" in r["Kernel_Name"]]
+        after = [r for r in rows[marks[1] + 1:] if "ConvFwd" in r["Kernel_Name"]]
         line = None
         if log_path:
             for l in open(log_path):
@@ -780,7 +780,7 @@ def summarize_counters(csv_path):
         if i <= start:
             continue
         name = disp[i]["name"]
-        k = "conv forward GEMM" if "ConvFwdProb" in name else \
+        k = "conv forward GEMM" if "ConvFwd" in name else \
             "conv weight-gradient GEMM" if "ConvWgrad" in name \
             else "conv data-gradient GEMM" if "ConvDgrad" in name else "dense GEMM" if "DenseProb" in name \
             else _short(name)
