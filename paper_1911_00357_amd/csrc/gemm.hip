@@ -288,12 +288,17 @@ int gemm_max_splits_for(long M, long N, long K, int prec) {
   return splits_for((long)cdiv(M, d.bm) * cdiv(N, d.bn), K);
 }
 
+// The scalar-tap loaders form the offset of an element of a batch of maps in 32
+// bits; the general ones that of its map, and add the rest in 64.  So the former
+// take batches of up to 2^31 elements, whose last offset still fits.
+static bool offsets_fit(long B, long H, long W, long C) { return B * H * W * C <= 1L << 31; }
+
 int gemm_conv_fwd(int prec, const ConvGeo& g, const float* x, const void* w, Epi e, size_t pb,
                   float* partial, hipStream_t s, bool defer) {
   const int M = g.B * g.Ho * g.Wo, N = g.Co, K = g.KH * g.KW * g.C;
   const FastDiv dC = fast_div(g.C), dKW = fast_div(g.KW), dHoWo = fast_div(g.Ho * g.Wo), dWo = fast_div(g.Wo);
   // a K tile of 32 in one tap, weight rows on 16 bytes
-  if (g.C % BK == 0 && (((uintptr_t)x | (uintptr_t)w) & 15) == 0) {
+  if (g.C % BK == 0 && (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && offsets_fit(g.B, g.H, g.W, g.C)) {
     if (prec == 1)
       return run<ConvFwdUProb<bf16_t>, bf16_t, false>({g, dC, dKW, dHoWo, dWo, x, (const bf16_t*)w, M, N, K}, e, pb,
                                                       partial, s, 1, defer);
@@ -368,7 +373,7 @@ void gemm_conv_dgrad(int prec, const ConvGeo& g, const float* dy, const void* w,
         continue;
       }
       const FastDiv dCo = fast_div(g.Co), dNkw = fast_div(nkw), dHqWq = fast_div(Hq * Wq), dWq = fast_div(Wq);
-      if (g.Co % BK == 0 && (((uintptr_t)dy | (uintptr_t)wt) & 15) == 0) {
+      if (g.Co % BK == 0 && (((uintptr_t)dy | (uintptr_t)wt) & 15) == 0 && offsets_fit(g.B, g.Ho, g.Wo, g.Co)) {
         if (prec == 1)
           run<ConvDgradUProb<bf16_t>, bf16_t, true>({g, dCo, dNkw, dHqWq, dWq, dy, (const bf16_t*)wt, M, N, K, step, rh, rw, kh0,
                                                      kw0, nkw, Wq}, ec, pb, partial, s, 1);
