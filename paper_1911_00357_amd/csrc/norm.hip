@@ -100,6 +100,12 @@ __global__ void __launch_bounds__(256) gn_finalize_kernel(const float4* __restri
 struct GnDiv {
   FastDiv c4, p, cg;
 };
+// Workgroups of a pass over n4 quads: a quad a thread, or 8192 workgroups where a
+// step of that many threads would take the 32-bit index past 2^31.
+static int quad_blocks(size_t n4) {
+  const size_t nb = std::min<size_t>(1 << 20, (n4 + 255) / 256);
+  return n4 + 256 * nb <= 1ull << 31 ? (int)nb : 8192;
+}
 static GnDiv gn_div(int P, int C, int G) { return GnDiv{fast_div(C / 4), fast_div(P), fast_div(C / G)}; }
 
 // (y - mean) rstd gamma + beta as gn_apply_kernel forms it, and as
@@ -151,7 +157,7 @@ void launch_gn_forward(const float* y, int B, int P, int C, int G, float eps, co
   hipLaunchKernelGGL(gn_finalize_kernel, dim3(cdiv((long)B * G, 4)), dim3(256), 0, s, part, B, S, C,
                      G, eps, stats);
   const size_t n4 = (size_t)B * P * C / 4;
-  const int nb = (int)std::min<size_t>(1 << 20, (n4 + 255) / 256);
+  const int nb = quad_blocks(n4);
   hipLaunchKernelGGL(gn_apply_kernel, dim3(nb), dim3(256), 0, s, y, (int)n4, P, C, G, gn_div(P, C, G), stats, gamma,
                      beta, res, relu, out, out_chw);
 }
@@ -368,7 +374,7 @@ void launch_gn_backward(const float* dout, const float* out, GnMask mask, int ch
                         float* dres, float* dgamma, float* dbeta, float2* bpart, float2* coef, int S,
                         hipStream_t s) {
   const size_t n = (size_t)B * P * C / 4;
-  const int nb = (int)std::min<size_t>(1 << 20, (n + 255) / 256);
+  const int nb = quad_blocks(n);
   auto run = [&](auto partial, auto apply) {
     hipLaunchKernelGGL(partial, dim3(S, B), dim3(256), 0, s, dout, out, chw, y, P, C, G, S, stats, gamma, beta,
                        bpart);
@@ -543,7 +549,8 @@ void launch_prep(const void* obs, int bf16, const int32_t* src, int F, int C, in
                  int pool, float* x0, hipStream_t s) {
   const int Ho = pool ? Hin / 2 : Hin, Wo = pool ? Win / 2 : Win;
   const size_t n = (size_t)F * Ho * Wo * C;
-  if (pool && C == 4 && Win % 2 == 0 && ((uintptr_t)obs & (bf16 ? 3 : 7)) == 0 && n / 4 < (1u << 31)) {
+  if (pool && C == 4 && Win % 2 == 0 && ((uintptr_t)obs & (bf16 ? 3 : 7)) == 0 &&
+      n / 4 <= (1u << 31) - 256 * 8192) {  // pixel index plus one step of the grid in 32 bits
     const int np = (int)(n / 4), nb = (int)std::min<size_t>(8192, ((size_t)np + 255) / 256);
     if (bf16)
       hipLaunchKernelGGL(prep4_kernel<bf16_t>, dim3(nb), dim3(256), 0, s, (const bf16_t*)obs, src, np, Hin, Win,

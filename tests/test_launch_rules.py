@@ -26,3 +26,30 @@ out = [[n for n, _ in act(h, {most})], [n for n, _ in act(h, {most + 1})],
         assert count(names, "ConvFwdUProb") == uniform and count(names, "ConvFwdProb") == 2 - uniform
     for names, uniform in zip(out[2:], (1, 0)):   # stride 2: four classes of input pixels
         assert count(names, "ConvDgradUProb") == 4 * uniform and count(names, "ConvDgradProb") == 4 * (1 - uniform)
+
+
+def test_groupnorm_passes_stay_within_32_bit_indices(tmp_path_factory):
+    """The GroupNorm passes step a 32-bit quad index by their grid: index plus
+    one step stays within 2^31 up to 2^31 - 2^21 quads, the most that 8192
+    workgroups can step.  This net's convolutions put out 4 and 1024 quads a frame."""
+    frames = [1 << 20, (1 << 21) - (1 << 18), (1 << 21) - (1 << 18) + 1, (1 << 21) - (1 << 11)]
+    out = record(tmp_path_factory, f"""
+h = net("f32", trunk=L.PPO_TRUNK_TINY, in_ch=1, in_hw=4, avgpool=0, tiny_ch=(4, 4096), gn_groups=4)
+grids = lambda ls, what: [g for n, g in ls if what in n]
+out = [[grids(act(h, f), "gn_apply"), grids(loss_backward(h, f), "gnb_apply")] for f in {frames}]
+""")
+    for f, (fwd, bwd) in zip(frames, out):
+        for quads, grid in zip((4 * f, 1024 * f, 1024 * f, 4 * f), fwd + bwd, strict=True):
+            assert quads + 256 * grid <= 1 << 31, (f, quads, grid)
+            assert grid == 8192 or grid == min(1 << 20, -(-quads // 256))
+
+
+def test_pooling_frame_prep_stays_within_32_bit_indices(tmp_path_factory):
+    """The pixel-wide frame prep steps a 32-bit pixel index by 8192 workgroups;
+    past 2^31 - 2^21 output pixels the elementwise form runs.  4 pixels a frame."""
+    most = ((1 << 31) - (1 << 21)) // 4
+    out = record(tmp_path_factory, f"""
+h = net("f32", trunk=L.PPO_TRUNK_TINY, in_hw=4, avgpool=1, tiny_ch=(4, 4), gn_groups=4)
+out = [act(h, f)[0][0] for f in ({most}, {most + 1})]
+""")
+    assert "prep4_kernel" in out[0] and "prep_kernel" in out[1]
