@@ -84,7 +84,7 @@ struct ppo_net {
   // ppo_collect's captured act loops, keyed on the call's arguments, oldest first
   std::unordered_map<std::string, hipGraphExec_t> graphs;
   std::deque<std::string> graph_order;
-  int cap_device = -1;        // the device those graphs live on
+  int cap_device = -1;        // the device those graphs live on (while there are any)
 };
 
 // Makes the net's tile table visible to the GEMM launchers for one call.
@@ -1015,7 +1015,7 @@ ppo_status ppo_collect(ppo_net* net, const ppo_collect_io* io, int flags, void* 
   if (trim) put(rows.data(), rows.size() * sizeof(int));
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return check_launch();
-  if (net->cap_device >= 0 && net->cap_device != dev)
+  if (!net->graphs.empty() && net->cap_device != dev)
     return fail(PPO_EINVAL, "the net's act graphs live on device %d, not %d", net->cap_device, dev);
   auto hit = net->graphs.find(key);
   if (hit != net->graphs.end()) {
@@ -1030,7 +1030,6 @@ ppo_status ppo_collect(ppo_net* net, const ppo_collect_io* io, int flags, void* 
   // 256 frames at 256x256 bfloat16: 27.4 ms instead of 15.5 ms)
   hipStream_t cap = nullptr;
   if (hipStreamCreateWithFlags(&cap, hipStreamNonBlocking) != hipSuccess) return check_launch();
-  net->cap_device = dev;
   collect_drop(net, kMaxCollectGraphs - 1);
   // the launch timer stays out of captured graphs (its events are re-armed and destroyed by the host)
   const int tu = net->timer_unit;
@@ -1053,6 +1052,7 @@ ppo_status ppo_collect(ppo_net* net, const ppo_collect_io* io, int flags, void* 
   (void)hipGetLastError();
   if (st != PPO_OK) return st;
   net->graphs.emplace(key, exec);
+  net->cap_device = dev;
   net->graph_order.push_back(key);
   return PPO_OK;
 }

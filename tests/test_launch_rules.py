@@ -53,3 +53,24 @@ h = net("f32", trunk=L.PPO_TRUNK_TINY, in_hw=4, avgpool=1, tiny_ch=(4, 4), gn_gr
 out = [act(h, f)[0][0] for f in ({most}, {most + 1})]
 """)
     assert "prep4_kernel" in out[0] and "prep_kernel" in out[1]
+
+
+def test_act_graphs_pin_the_net_only_while_there_are_any(tmp_path_factory):
+    """A net's act graphs live on one device: a graph-mode call on another is
+    refused while there is one, and not after a capture that failed or once they
+    were cleared."""
+    out = record(tmp_path_factory, """
+def collect(h, device, fail=0):
+    io = L.CollectIO(T=2, N=2, t_begin=0, t_end=3)
+    for f in "obs goal mask u params params_lp actions logp value h_hist c_hist h_last c_last".split():
+        setattr(io, f, FAKE)
+    C.c_int.in_dll(rec, "rec_device").value = device
+    C.c_int.in_dll(rec, "rec_fail_capture").value = fail
+    return lib.ppo_collect(h, C.byref(io), L.PPO_COLLECT_GRAPH, FAKE, 1 << 62, None)
+h = net("f32", trunk=L.PPO_TRUNK_TINY, in_hw=32, avgpool=0)
+count = lambda: lib.ppo_collect_graph_count(h)
+out = [collect(h, 0, fail=1), count(), collect(h, 1), count(), collect(h, 0), count(), collect(h, 1),
+       lib.ppo_collect_clear(h), collect(h, 0), count(), collect(h, 1)]
+""")
+    EDEVICE, EINVAL, OK = -5, -1, 0
+    assert out == [EDEVICE, 0, OK, 1, EINVAL, 1, OK, 1, OK, 1, EINVAL]
