@@ -108,9 +108,11 @@ static int quad_blocks(size_t n4) {
 }
 static GnDiv gn_div(int P, int C, int G) { return GnDiv{fast_div(C / 4), fast_div(P), fast_div(C / G)}; }
 
-// (y - mean) rstd gamma + beta as gn_apply_kernel forms it, and as
-// gn_fused_kernel does (which adds a 0 residual, of no effect on the sign): the
-// backward recomputes the ReLU mask of units without a residual with them.
+// (y - mean) rstd gamma + beta: what gn_apply_kernel puts out, and what
+// gn_fused_kernel does (which adds a 0 residual, of no effect on the sign).  The
+// backward recomputes the ReLU mask of units without a residual with the same
+// functions, each operation spelled out, so that the two agree at the border
+// whatever the compiler contracts elsewhere.
 DEV float gn_value(float y, float2 st, float gamma, float beta) {
   return fmaf((y - st.x) * st.y, gamma, beta);
 }
@@ -712,10 +714,11 @@ __global__ void __launch_bounds__(NT) gn_fused_kernel(const float* __restrict__ 
       }
     const float2 v12 = block_sum2<NT>(q1, q2, red2);
     const float rstd2 = 1.0f / sqrtf(v12.y / n + eps);
-    if (threadIdx.x == 0) stats2[blockIdx.x] = make_float2(mean2, rstd2);
-    const float ga2 = gamma2[c] * rstd2, be2 = beta2[c];
+    const float2 st2 = make_float2(mean2, rstd2);
+    if (threadIdx.x == 0) stats2[blockIdx.x] = st2;
+    const float gamma2c = gamma2[c], be2 = beta2[c];
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) rv[j] = (x2[j] - mean2) * ga2 + be2 + 0.f;
+    for (int j = 0; j < NPT; ++j) rv[j] = gn_value_fused(x2[j], st2, gamma2c, be2) + 0.f;
     mean = mean1;       // this GroupNorm's statistics from the same sums as a launch of its own
     var = v12.x / n;
   } else {
@@ -727,14 +730,14 @@ __global__ void __launch_bounds__(NT) gn_fused_kernel(const float* __restrict__ 
     var = block_sum<NT>(q, red) / n;
   }
   const float rstd = 1.0f / sqrtf(var + eps);
-  if (threadIdx.x == 0) stats[blockIdx.x] = make_float2(mean, rstd);
-  const float ga = gm * rstd;
+  const float2 st = make_float2(mean, rstd);
+  if (threadIdx.x == 0) stats[blockIdx.x] = st;
 #pragma unroll
   for (int j = 0; j < NPT; ++j) {
     const int p = p0 + j * pstep;
     if (p < P) {
       const size_t idx = base + j * jstr;
-      float o = (x[j] - mean) * ga + be + rv[j];
+      float o = gn_value_fused(x[j], st, gm, be) + rv[j];
       if (relu) o = fmaxf(o, 0.f);
       if (pool_out)
         s_slab[p * Cg + cc] = o;
