@@ -74,3 +74,23 @@ out = [collect(h, 0, fail=1), count(), collect(h, 1), count(), collect(h, 0), co
 """)
     EDEVICE, EINVAL, OK = -5, -1, 0
     assert out == [EDEVICE, 0, OK, 1, EINVAL, 1, OK, 1, OK, 1, EINVAL]
+
+
+@pytest.mark.parametrize("fwd", ["one_launch", "three_launch"])
+def test_groupnorm_backward_takes_its_mask_as_the_forward_formed_it(tmp_path_factory, fwd):
+    """Three-launch backward: units with a residual are masked by the saved
+    output (1), projection shortcuts not at all (0), the others by the value
+    formed again as the forward's kernel formed it (one-launch 3, three-launch
+    2).  Group widths that divide 256, so the one-launch form takes every unit:
+    the stem and the compression among them."""
+    out = record(tmp_path_factory, """
+h = net("f32", in_hw=64, base_width=8, gn_groups=2, compress_ch=8)
+out = [n for n, _ in loss_backward(h, 7) if "gn" in n]
+""", {"DDPPO_GN_FUSED_MAX": "0" if fwd == "three_launch" else str(1 << 30), "DDPPO_GNB_FUSED_MAX": "0"})
+    fused = sum("gn_fused_kernel" in n for n in out)
+    assert fused == (18 if fwd == "one_launch" else 0)   # stem, 4 x (c1, c2, c3, ds), compression
+    for kernel in ("gnb_partial_kernel", "gnb_apply_kernel"):
+        masks = [int(n.split("ILi")[1].split("E")[0]) for n in out if kernel in n]
+        want = 3 if fwd == "one_launch" else 2
+        block = [1, want, want, 0]                       # c3, c2, c1, ds
+        assert masks == [want] + 4 * block + [want], kernel
