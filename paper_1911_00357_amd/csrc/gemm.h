@@ -12,7 +12,7 @@
 // lanes of a wavefront walk the rows so each of the 8 scalar loads is
 // coalesced; either way the chunk lands in LDS with one 16-byte write.
 // The weight gradient reads 4 rows x 4 k as four row vectors and transposes
-// them in registers (QUADS).
+// them in registers (QUADS), or 8 rows x 2 k stored as pairs (RT).
 //
 // bfloat16: v_mfma_f32_32x32x16_bf16 on 32x32 fragments.  float32: four
 // v_mfma_f32_16x16x4_f32 per 16-k step on 16x16 fragments.  A and B use the
@@ -419,7 +419,7 @@ struct ConvWgradProb {
 // gained nothing): a quarter of the loads and index arithmetic of the scalar
 // gather, the same conversions.  All weight gradients of 256 frames (54
 // launches): bfloat16 3.01 -> 1.95 ms, float32 4.25 -> 3.21 ms (its stem alone, 4
-// channels a tap, is slower than 8-row vectors stored transposed: 317 -> 360 us).
+// channels a tap, was slower so, 317 -> 360 us, and takes 8-row vectors again: below).
 // Needs Co % 4 == 0, C % 4 == 0 and 16-byte aligned x and dy.
 struct ConvWgradQProb {
   static constexpr int kKind = 3;
@@ -477,6 +477,62 @@ struct ConvWgradQProb {
   }
 };
 
+// Weight gradient with 8-row vectors: a unit is 8 consecutive rows m..m+7 (output
+// channels for A, (kh,kw,ci) for B: two taps of 4 channels where C is not 8n) at
+// reduction indices k and k+1, two float4 loads each, stored down the LDS rows as
+// pairs along k (put8t2).  Needs Co % 8 == 0, C % 4 == 0, 16-byte aligned x and dy.
+// Float32, where the quads fit the tile badly (see the dispatch); the loads of
+// both k of all units go out before the first is used: the stem of 256 frames
+// 300 us when they went out unit by unit, 232 us so.
+struct ConvWgradRTProb {
+  static constexpr int kKind = 4;
+  ConvGeo g;
+  FastDiv dHoWo, dWo;
+  const float* x;
+  const float* dy;
+  int M, N, K;  // as ConvWgradProb
+  struct RA {
+    int co, ok;
+  };
+  struct RB {
+    int kh0, kw0, ci0, kh1, kw1, ci1, nv;  // taps of rows n..n+3 and n+4..n+7; rows within N (0, 4 or 8)
+  };
+  DEV RA rowA(int m) const { return RA{m, m < M}; }
+  DEV RB rowB(int n) const {
+    const int t0 = n / g.C, t1 = (n + 4) / g.C;
+    RB r;
+    r.nv = max(0, min(8, N - n));
+    r.ci0 = n - t0 * g.C;
+    r.kh0 = t0 / g.KW;
+    r.kw0 = t0 - r.kh0 * g.KW;
+    r.ci1 = n + 4 - t1 * g.C;
+    r.kh1 = t1 / g.KW;
+    r.kw1 = t1 - r.kh1 * g.KW;
+    return r;
+  }
+  DEV void a8(const RA& r, int k, float v[8]) const {
+    if (!r.ok || k >= K) return zero8(v);
+    load8(dy + (size_t)k * g.Co + r.co, v);
+  }
+  DEV void b8(const RB& r, int k, float v[8]) const {
+    zero8(v);
+    if (r.nv <= 0 || k >= K) return;
+    const int b = dHoWo.div(k), q = k - b * g.Ho * g.Wo;
+    const int ho = dWo.div(q), wo = q - ho * g.Wo;
+    const int hb = ho * g.stride - g.pad, wb = wo * g.stride - g.pad;
+    const float* xb = x + (size_t)b * g.H * g.W * g.C;
+    auto quad = [&](int kh, int kw, int ci, float* o) {
+      const int hi = hb + kh, wi = wb + kw;
+      if ((unsigned)hi < (unsigned)g.H && (unsigned)wi < (unsigned)g.W) {
+        const float4 t = *(const float4*)(xb + ((size_t)hi * g.W + wi) * g.C + ci);
+        o[0] = t.x; o[1] = t.y; o[2] = t.z; o[3] = t.w;
+      }
+    };
+    quad(r.kh0, r.kw0, r.ci0, v);
+    if (r.nv > 4) quad(r.kh1, r.kw1, r.ci1, v + 4);
+  }
+};
+
 // Dense: A(m, k) = a[m*lda + k] (or a[k*lda + m] when TA), B(n, k) = b[n*ldb + k]
 // (or b[k*ldb + n] when TB).
 template <typename TAe, typename TBe, bool TA, bool TB>
@@ -522,29 +578,32 @@ template <typename TW> struct WeightBytes<ConvFwdUProb<TW>> { static constexpr i
 
 // Is the operand contiguous along rows (so lanes should walk rows)?  QUADS:
 // units are 4 rows x 4 k (vector loads along rows, transposed in registers).
-// UNI: a K tile lies in one tap.
+// RT: units are 8 rows x 2 k.  UNI: a K tile lies in one tap.
 template <class P> struct Layout;
 template <> struct Layout<ConvWgradQProb> {
-  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = true, UNI = false;
+  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = true, RT = false, UNI = false;
+};
+template <> struct Layout<ConvWgradRTProb> {
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, RT = true, UNI = false;
 };
 template <typename TW> struct Layout<ConvFwdProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = false;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, RT = false, UNI = false;
 };
 template <typename TW> struct Layout<ConvDgradProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = false;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, RT = false, UNI = false;
 };
 template <typename TW> struct Layout<ConvFwdUProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = true;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, RT = false, UNI = true;
 };
 template <typename TW> struct Layout<ConvDgradUProb<TW>> {
-  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, UNI = true;
+  static constexpr bool A_ROWS = false, B_ROWS = false, QUADS = false, RT = false, UNI = true;
 };
 template <> struct Layout<ConvWgradProb> {
-  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = false, UNI = false;
+  static constexpr bool A_ROWS = true, B_ROWS = true, QUADS = false, RT = false, UNI = false;
 };
 template <typename A_, typename B_, bool TA, bool TB>
 struct Layout<DenseProb<A_, B_, TA, TB>> {
-  static constexpr bool A_ROWS = TA, B_ROWS = TB, QUADS = false, UNI = false;
+  static constexpr bool A_ROWS = TA, B_ROWS = TB, QUADS = false, RT = false, UNI = false;
 };
 // Tile-table kind of a problem.
 template <class P> int kind_of(const P&) { return P::kKind; }
@@ -640,6 +699,14 @@ DEV void put44(bf16_t* d, int ld, const float4 v[4], bf16_t* lo) {
       *(uint2*)(lo + j * ld) = make_uint2(l0, l1);
     }
   }
+}
+
+// 8 rows at k and k+1 (k even) -> columns k, k+1 of 8 consecutive LDS rows (stride
+// ld): a pair a row.  The lanes of a wavefront walk k, so a store instruction
+// covers consecutive LDS words of a row.
+DEV void put8t2(float* d, int ld, const float v0[8], const float v1[8]) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) *(float2*)(d + e * ld) = make_float2(v0[e], v1[e]);
 }
 
 // ------------------------------------------------------------- kernel
@@ -742,6 +809,48 @@ __global__ void __launch_bounds__(256) gemm_kernel(Prob p, Epi e, int tiles_n, i
       for (int q = 0; q < QU; ++q) {
         if (is_a(q)) put44(&sA[0][buf][uo[q]], LDK, vu[q], SPLIT ? &sA[NSPL - 1][buf][uo[q]] : (TC*)nullptr);
         else if (live(q)) put44(&sB[buf][uo[q]], LDK, vu[q], (TC*)nullptr);
+      }
+    };
+    mainloop(gload, sstore);
+  } else if constexpr (Layout<Prob>::RT) {
+    constexpr int RA_ = BM / 8 * (BK / 2), RB_ = BN / 8 * (BK / 2);  // units of A and B
+    constexpr int PA = (RA_ + 255) / 256, PB = (RB_ + 255) / 256;
+    auto row = [](int c) { return c / (BK / 2) * 8; };
+    auto kc = [](int c) { return c % (BK / 2) * 2; };
+    typename Prob::RA ra[PA];
+    typename Prob::RB rb[PB];
+    float va[PA][2][8], vb[PB][2][8];
+#pragma unroll
+    for (int q = 0; q < PA; ++q) ra[q] = p.rowA(tid + 256 * q < RA_ ? m0 + row(tid + 256 * q) : 1 << 30);
+#pragma unroll
+    for (int q = 0; q < PB; ++q) rb[q] = p.rowB(tid + 256 * q < RB_ ? n0 + row(tid + 256 * q) : 1 << 30);
+    auto gload = [&](int k0) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int q = 0; q < PA; ++q) {
+          const int c = tid + 256 * q, k = k0 + kc(c) + h;
+          if (c < RA_ && k < kend) p.a8(ra[q], k, va[q][h]);
+          else zero8(va[q][h]);
+        }
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
+          const int c = tid + 256 * q, k = k0 + kc(c) + h;
+          if (c < RB_ && k < kend) p.b8(rb[q], k, vb[q][h]);
+          else zero8(vb[q][h]);
+        }
+      }
+    };
+    auto sstore = [&](int buf) {
+#pragma unroll
+      for (int q = 0; q < PA; ++q) {
+        const int c = tid + 256 * q;
+        if (c < RA_) put8t2(&sA[0][buf][row(c) * LDK + kc(c)], LDK, va[q][0], va[q][1]);
+      }
+#pragma unroll
+      for (int q = 0; q < PB; ++q) {
+        const int c = tid + 256 * q;
+        if (c < RB_) put8t2(&sB[buf][row(c) * LDK + kc(c)], LDK, vb[q][0], vb[q][1]);
       }
     };
     mainloop(gload, sstore);

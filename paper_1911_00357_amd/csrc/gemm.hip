@@ -400,6 +400,15 @@ void gemm_conv_wgrad(int prec, const ConvGeo& g, const float* x, const float* dy
   // channel quads wherever every quad is one aligned vector of one tap; an
   // input of other than 4n channels takes scalar loads
   if (g.Co % 4 == 0 && g.C % 4 == 0 && (((uintptr_t)x | (uintptr_t)dy) & 15) == 0) {
+    // Float32, at most 32 output channels, more than 64 columns, channels 4n but
+    // not 8n (the stem): the quads' 64-row tile would pad half its rows or the
+    // 32x128 one idle its threads, 8-row vectors fill the latter.  256 frames, us,
+    // quads against these: 128x128x4 -> 32, 7x7 324, 232; 32x32x20 -> 32, 3x3 88,
+    // 65; but 32x32x4 -> 32, 3x3 (36 columns) 44, 47; 32x32x20 -> 40, 3x3 85, 95.
+    if (prec == 0 && M <= 32 && N > 64 && g.Co % 8 == 0 && g.C % 8 != 0) {
+      run<ConvWgradRTProb, float, false>({g, fast_div(g.Ho * g.Wo), fast_div(g.Wo), x, dy, M, N, K}, e, pb, partial, s, 0);
+      return;
+    }
     ConvWgradQProb p{g, fast_div(g.C), fast_div(g.KW), fast_div(g.Ho * g.Wo), fast_div(g.Wo), x, dy, M, N, K,
                      g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0};
     run_prec(p, e, prec, true, pb, partial, s);

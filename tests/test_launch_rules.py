@@ -94,3 +94,20 @@ out = [n for n, _ in loss_backward(h, 7) if "gn" in n]
         want = 3 if fwd == "one_launch" else 2
         block = [1, want, want, 0]                       # c3, c2, c1, ds
         assert masks == [want] + 4 * block + [want], kernel
+
+
+@pytest.mark.parametrize("dtype,in_ch,width,rt", [("f32", 4, 32, 1), ("f32", 12, 8, 1), ("f32", 8, 32, 0),
+                                                  ("f32", 4, 64, 0), ("f32", 4, 4, 0), ("f32", 3, 32, 0),
+                                                  ("bf16", 4, 32, 0)])
+def test_float32_stem_weight_gradient_takes_row_vectors(tmp_path_factory, dtype, in_ch, width, rt):
+    """8-row vectors for a float32 stem of at most 32 (8n) output channels on 4n
+    but not 8n input channels; scalar loads where they are not 4n; channel quads
+    elsewhere (bottleneck units among them)."""
+    out = record(tmp_path_factory, f"""
+h = net("{dtype}", in_ch={in_ch}, base_width={width}, gn_groups=4)
+out = [n for n, _ in loss_backward(h, 4) if "ConvWgrad" in n]
+""")
+    stem = out[-1]                                       # the last weight gradient of a backward
+    kind = "ConvWgradRTProb" if rt else "ConvWgradProb" if in_ch % 4 else "ConvWgradQProb"
+    assert kind in stem and sum(kind in n for n in out) >= 1
+    assert sum("ConvWgradRTProb" in n for n in out) == rt
