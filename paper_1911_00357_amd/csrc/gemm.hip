@@ -105,8 +105,8 @@ Tile launch_tile_of(Tile t, long M, long N, long K, int splits, int prec, bool q
       (long)cdiv(M, dim_of(t).bm) * cdiv(N, dim_of(t).bn) * splits < 256)
     return T64x64;
   // Others: with few K tiles a workgroup is mostly its first loads and its
-  // stores, and smaller tiles keep more of them in flight per CU (LDS 25 KB
-  // against 60).  bfloat16, M x N x K:
+  // stores, and smaller tiles keep more of them in flight per CU (LDS with split
+  // operands: 30 KB against 60).  bfloat16, M x N x K:
   //   N <= 64 (65536 x 64 x 256: 128x64 29, 64x64 22; x 576: 37, 35)
   if (prec == 1 && t == T128x64) return T64x64;
   //   wide, K < 128 (262144 x 128 x 32 data gradient: 128x128 171, 64x64 98, 64x128 106)

@@ -8,9 +8,13 @@
 //                            a dense 3x3 and its per-group products (K = 9C/G,
 //                            N = Co/G, as small as 36 x 4) would leave most of
 //                            a matrix-core tile empty, so it is a direct
-//                            vector-ALU convolution bound by the activation
-//                            traffic: one workgroup per (pixel tile, group)
-//                            with the group's filters staged in LDS.
+//                            vector-ALU convolution, bound by its multiply-adds
+//                            and the LDS and L1 reads that feed them: one workgroup
+//                            per (pixel tile, one to four neighbouring groups) with
+//                            their filters staged in LDS.  Groups of 4, 8, 16 or 32
+//                            channels on both sides run register-tiled kernels
+//                            (several outputs a thread), others a general form
+//                            with one output a thread.
 //   squeeze-excite           z = per-channel pixel mean of the branch y,
 //                            s = sigmoid(W2 relu(W1 z + b1) + b2), then
 //                            out = relu(s * y + shortcut); the FCs are tiny
@@ -259,7 +263,8 @@ __global__ void __launch_bounds__(kThreads) gconv_wgrad_kernel(const float* __re
 // which bounds them; these read a float4 for 4 to 8 FMAs.
 //
 // Forward and data gradient (BWD; source dy, filters transposed).  Workgroup:
-// `pix` pixels of gpw neighbouring groups (64 to 128 contiguous bytes a pixel);
+// `pix` pixels of gpw neighbouring groups (64 contiguous bytes a pixel, 128 at CG
+// 32; 16 or 32 at CG 4 and 8 where the group count has no such factor);
 // a thread makes 4 channels of NP pixels (2, or 1 where that would leave the
 // chip idle).  Filters in LDS as ws[group][tap][source channel][channel], 16
 // floats of padding a group against conflicts between groups.  128 frames of
