@@ -761,8 +761,9 @@ def act_step_positions(act, dur):
 
 
 def summarize_counters(csv_path):
-    """Per kernel class, summed counters of the dispatches after the landmark
-    of a --pmc-probe run (the copy before it is the calibration): JSON."""
+    """Per kernel class (the stem's weight gradient, the first of the learner
+    probe, by itself), summed counters of the dispatches after the landmark of a
+    --pmc-probe run (the copy before it is the calibration): JSON."""
     import collections
     import csv
     rows = list(csv.DictReader(open(csv_path)))
@@ -780,8 +781,9 @@ def summarize_counters(csv_path):
         if i <= start:
             continue
         name = disp[i]["name"]
+        wgrad = "conv weight-gradient GEMM"
         k = "conv forward GEMM" if "ConvFwd" in name else \
-            "conv weight-gradient GEMM" if "ConvWgrad" in name \
+            (wgrad if wgrad in cls or "stem " + wgrad in cls else "stem " + wgrad) if "ConvWgrad" in name \
             else "conv data-gradient GEMM" if "ConvDgrad" in name else "dense GEMM" if "DenseProb" in name \
             else _short(name)
         cls[k]["dispatches"] += 1

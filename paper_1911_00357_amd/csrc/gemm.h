@@ -415,9 +415,11 @@ struct ConvWgradProb {
 // Weight gradient with channel quads: a unit is 4 consecutive channels (co for
 // A, ci of one tap for B) at 4 consecutive reduction indices r = (b,ho,wo),
 // four float4 loads along the NHWC channel axis, coalesced over the lanes.
-// Bound by vector instructions, not by memory latency (two K tiles in flight
-// gained nothing): a quarter of the loads and index arithmetic of the scalar
-// gather, the same conversions.  All weight gradients of 256 frames (54
+// A quarter of the loads and index arithmetic of the scalar gather, the same
+// conversions: 28 vector instructions a matrix instruction (counted, bfloat16,
+// 256 frames), 81 before.  Of what is left the wavefronts wait 62 % of their
+// cycles, for a K tile's loads and at its barrier; two tiles in flight gained
+// nothing (float32) or spilled (bfloat16).  All weight gradients of 256 frames (54
 // launches): bfloat16 3.01 -> 1.95 ms, float32 4.25 -> 3.21 ms (its stem alone, 4
 // channels a tap, was slower so, 317 -> 360 us, and takes 8-row vectors again: below).
 // Needs Co % 4 == 0, C % 4 == 0 and 16-byte aligned x and dy.
