@@ -731,7 +731,7 @@ def act_step_positions(act, dur):
     import collections
     steps, cur = [], []
     for r in act:
-        if "prep_kernel<" in r["Kernel_Name"] and "core_prep" not in r["Kernel_Name"] and cur:
+        if any(k in r["Kernel_Name"] for k in ("prep_kernel<", "prep4_kernel<")) and cur:
             steps.append(cur)
             cur = []
         cur.append(r)
